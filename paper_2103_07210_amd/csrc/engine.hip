@@ -253,7 +253,7 @@ Layout layout(const ftgcr_handle* h)
     L.xvec = align256(n * sizeof(double));
     L.part = align256((size_t)part_stride(h) * NV_MAX * sizeof(double));
     L.hist = align256((size_t)std::max<long long>(h->opt.hist_cap, 1) * sizeof(double));
-    // P, AP (kmax + 1 each), three r, e, and on the octahedral mesh L(e)
+    // U (kmax + 2), AP (kmax + 1), three r, and on the octahedral mesh L(e)
     const int nvec = 2 * (h->kmax + 1) + 4 + (h->geo.mesh == FTGCR_MESH_OCTAHEDRAL ? 1 : 0);
     L.total = (size_t)nvec * L.vec + L.xvec + L.part + L.hist;
     return L;
@@ -267,10 +267,9 @@ Inst<T> make_inst(const ftgcr_handle* h, const double* rhs, double* x, void* ws)
     in.g = h->geo;
     const Layout L = layout(h);
     char* p = (char*)ws;
-    for (int l = 0; l <= h->kmax; ++l) { in.P[l] = (T*)p; p += L.vec; }
+    for (int l = 0; l <= h->kmax + 1; ++l) { in.U[l] = (T*)p; p += L.vec; }
     for (int l = 0; l <= h->kmax; ++l) { in.AP[l] = (T*)p; p += L.vec; }
     for (int q = 0; q < 3; ++q) { in.R[q] = (T*)p; p += L.vec; }
-    in.E = (T*)p; p += L.vec;
     if (h->geo.mesh == FTGCR_MESH_OCTAHEDRAL) {
         in.LE = (T*)p;
         p += L.vec;
@@ -1004,14 +1003,14 @@ ftgcr_status solve_impl(ftgcr_handle* h, const double* rhs, double* x, double to
 // ---------------------------------------------------------------------------
 
 // The GMRES working vectors inside the FP64 workspace layout: v_0..v_kmax in
-// the direction slots, z_0..z_{kmax-1} and w in the image slots.
+// the basis slots, z_0..z_{kmax-1} and w in the image slots.
 GmInst make_gm_inst(const ftgcr_handle* h, const double* rhs, double* x, void* ws)
 {
     const Inst<double> in = make_inst<double>(h, rhs, x, ws);
     GmInst gi;
     std::memset(&gi, 0, sizeof gi);
     gi.g = in.g;
-    for (int l = 0; l <= h->kmax; ++l) gi.U[l] = in.P[l];
+    for (int l = 0; l <= h->kmax; ++l) gi.U[l] = in.U[l];
     for (int l = 0; l < h->kmax; ++l) gi.Z[l] = in.AP[l];
     gi.W = in.AP[h->kmax];
     gi.X[0] = in.X[0];

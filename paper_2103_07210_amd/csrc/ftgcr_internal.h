@@ -83,18 +83,25 @@ struct SolveState {
     double d[KMAX + 1];
     double beta[KMAX + 1];
     double alpha[KMAX + 1];
-    int slot[KMAX + 1];  // buffer index of p^l / L(p^l)
+    // p^l = sum_{j <= l} bm[l][j] u_j over the cycle's basis u_0 = p^0,
+    // u_j = e of its j-th step (bm[l][l] = 1): the directions after p^0 are
+    // never stored, only p^k of a cycle's end, which opens the next one
+    double bm[KMAX + 1][KMAX + 1];
+    double xc[KMAX + 1]; // the cycle's iterate update sum_l beta_l p^l over the basis
+    int slot[KMAX + 1];  // buffer index of L(p^l)
+    int uslot[KMAX + 2]; // buffer index of u_l, l = 0..k; [k + 1]: where p^k is formed
     int r_cur, r_dst, r_bak;
     int x_base, x_base_nu, x_bak, x_dst;
-    int x_final_hi;      // materialise x with beta_l p^l for l <= this at the end
-    int b_slot0;
+    int x_final_hi;      // materialise x with beta_l p^l for l <= this at the end (basis sums)
+    int b_slot0, b_uslot0;
     long long b_accepted;
     double b_rr, b_beta_num, b_d0;
     // fault-event staging (set by the event preparation kernel)
     int ev_ok;           // the event applies (solve still running)
     int ev_vec;
-    int ev_copy;         // 1: copy src -> dst buffer before flipping
+    int ev_copy;         // 1: copy src -> dst buffer before flipping; 2: form p^nu in u_nu's
     int ev_src, ev_dst;  // buffer indices for the copy
+    int ev_usrc, ev_udst;   // and of p^0 with that of L(p^0)
     int ev_lo, ev_hi;    // x materialisation: beta terms l in [lo, hi)
     int log_len;
     int e_ok;            // 1: this step passed its tests, its e feeds a new direction
@@ -148,10 +155,9 @@ struct Geo {
 template <typename T>
 struct Inst {
     Geo g;
-    T* P[KMAX + 1];
+    T* U[KMAX + 2];          // the cycle's basis: p^0 and every e since (SolveState::bm)
     T* AP[KMAX + 1];
     T* R[3];
-    T* E;
     // octahedral mesh: L(e) of the step, stored by the dots pass and read by
     // the direction pass instead of a second indirect stencil (null on the
     // lat-lon mesh)

@@ -696,6 +696,26 @@ __device__ __forceinline__ void assign_slots(SolveState* st, int k)
         if (l != s0) st->slot[q++] = l;
 }
 
+// Basis buffers after uslot[0], `last` at the end: the first pass of a cycle
+// writes its e (uslot[1]) before the decision that retires the backup, so
+// the previous cycle's p^0 must not come first.
+__device__ __forceinline__ void assign_uslots(SolveState* st, int k, int last)
+{
+    const int s0 = st->uslot[0];
+    int q = 1;
+    for (int l = 0; l <= k + 1; ++l)
+        if (l != s0 && l != last) st->uslot[q++] = l;
+    if (last != s0) st->uslot[q] = last;
+}
+
+// sum_{l = lo .. hi} beta_l p^l over the basis: the coefficient of u_j.
+__device__ __forceinline__ double basis_coef(const SolveState* st, int j, int lo, int hi)
+{
+    double c = 0.0;
+    for (int l = lo > j ? lo : j; l <= hi; ++l) c = fma(st->beta[l], st->bm[l][j], c);
+    return c;
+}
+
 // ---------------------------------------------------------------------------
 // state setup
 // ---------------------------------------------------------------------------
@@ -731,7 +751,10 @@ __global__ void k_init_state(Table<T> tb, int k, int ft, int mixed, long long ma
         st->d[l] = 0.0;
         st->beta[l] = 0.0;
         st->alpha[l] = 0.0;
+        st->xc[l] = 0.0;
     }
+    for (int l = 0; l <= KMAX + 1; ++l) st->uslot[l] = l;
+    st->bm[0][0] = 1.0;
     st->r_cur = 0;
     st->r_dst = 0;
     st->r_bak = 0;
@@ -848,6 +871,8 @@ __device__ void rollback(SolveState* st)
 {
     st->slot[0] = st->b_slot0;
     assign_slots(st, st->k);
+    st->uslot[0] = st->b_uslot0;
+    assign_uslots(st, st->k, st->b_uslot0);
     st->r_cur = st->r_bak;
     st->r_dst = other_r(st->r_cur, st->r_cur);
     st->x_base = st->x_bak;
@@ -873,6 +898,7 @@ __device__ void decide_init(SolveState* st, double rn, double rs)
     st->b_rr = rs;
     st->b_accepted = st->accepted;
     st->b_slot0 = st->slot[0];
+    st->b_uslot0 = st->uslot[0];
     st->r_bak = st->r_cur;
     st->x_bak = st->x_base;
 }
@@ -940,6 +966,7 @@ __device__ void decide_step(SolveState* st, DetectRec* log, double rn, double rs
         st->b_d0 = st->d_cur;
         st->b_accepted = st->accepted;
         st->b_slot0 = st->slot[0];
+        st->b_uslot0 = st->uslot[0];
         st->r_bak = st->r_cur;
         st->x_bak = st->x_base;
     }
@@ -974,6 +1001,9 @@ __device__ void decide_beta(SolveState* st, double num, double dn, int init)
         st->x_base_nu = 0;
         st->slot[0] = st->slot[st->k];
         assign_slots(st, st->k);
+        const int old = st->uslot[0];
+        st->uslot[0] = st->uslot[st->k + 1];
+        assign_uslots(st, st->k, old);
         st->nu = 0;
         st->d[0] = dn;
         st->r_dst = other_r(st->r_cur, st->r_bak);
@@ -1059,7 +1089,7 @@ __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in,
         den = gm->st->den[jj];
     } else {
         rin = in.R[st->r_cur];
-        eout = in.E;
+        eout = in.U[st->uslot[mode == MODE_STEP ? st->nu + 1 : 0]];
         ap = rin;
         rout = nullptr;
         if (mode == MODE_STEP) {
@@ -1321,7 +1351,7 @@ __global__ __launch_bounds__(COL_THREADS) void k_update_thomas1(Table<T> tb)
         rout = in.R[st->r_dst];
         beta = -st->beta_num / st->d_cur;
     }
-    T* eout = in.E;
+    T* eout = in.U[st->uslot[mode == MODE_STEP ? st->nu + 1 : 0]];
     double* part = in.part;
     const long long pstride = in.pstride;
     __syncthreads();
@@ -1465,7 +1495,7 @@ __global__ __launch_bounds__(COL_THREADS) void k_update_copy(Table<T> tb, const 
         den = gm->st->den[jj];
     } else {
         rin = in.R[st->r_cur];
-        eout = in.E;
+        eout = in.U[st->uslot[mode == MODE_STEP ? st->nu + 1 : 0]];
         if (mode == MODE_STEP) {
             ap = in.AP[st->slot[st->nu]];
             rout = in.R[st->r_dst];
@@ -1541,7 +1571,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_stencil_dots(Table<T> tb, int sp
     const long long plane = (long long)in.g.ncols;
     const long long c0 = (long long)ps.i + (long long)in.g.nx * ps.j;
     double le[KC];
-    stencil_m<T, KC, MESH>(in.g, in.E, ps, le);
+    stencil_m<T, KC, MESH>(in.g, in.U[st->uslot[nu + 1]], ps, le);
 #pragma unroll
     for (int kk = 0; kk < KC; ++kk) {
         const bool ok = ps.col_ok && ps.k0 + kk < nz;
@@ -1606,14 +1636,26 @@ __global__ __launch_bounds__(ST_THREADS) void k_stencil_dots(Table<T> tb, int sp
     }
 }
 
-// alpha_l = -<L(e), L(p^l)> / <L(p^l), L(p^l)> and the iterate buffer the
-// direction pass writes; every thread of the block calls it.
+// alpha_l = -<L(e), L(p^l)> / <L(p^l), L(p^l)>, the new direction over the
+// basis (p^{nu+1} = e + sum_l alpha_l p^l), at a cycle's end the iterate
+// update over the basis, and the iterate buffer the direction pass writes;
+// every thread of the block calls it.
 template <typename T>
 __device__ __forceinline__ void finish_alpha_body(const Inst<T>& in, SolveState* st)
 {
     const int nu = st->nu;
     const double* v = sum_partials<4, 4>(in, in.nblk_st, DOT_ROW0, nu + 1, nullptr);
     if ((int)threadIdx.x <= nu) st->alpha[threadIdx.x] = -v[threadIdx.x] / st->d[threadIdx.x];
+    __syncthreads();
+    if ((int)threadIdx.x <= nu) {
+        const int j = threadIdx.x;
+        double c = 0.0;
+        for (int l = j; l <= nu; ++l) c = fma(st->alpha[l], st->bm[l][j], c);
+        st->bm[nu + 1][j] = c;
+        if (nu + 1 == st->k) st->xc[j] = basis_coef(st, j, st->x_base_nu, nu);
+    } else if ((int)threadIdx.x == nu + 1) {
+        st->bm[nu + 1][nu + 1] = 1.0;
+    }
     if (threadIdx.x == 0) st->x_dst = (st->x_base == st->x_bak) ? 1 - st->x_base : st->x_base;
 }
 
@@ -1655,8 +1697,14 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_step(Table<T> tb)
 // new direction, its image, next beta's inner products, deferred iterate
 // ---------------------------------------------------------------------------
 
-// Cache hints: the p^l, the iterate and the new p^{nu+1} are next touched
-// a whole step later (more than the Infinity Cache holds in between), so
+// The directions are not formed step by step: p^{nu+1} = e + sum_l alpha_l p^l
+// is a row of bm over the cycle's basis, so the pass forms L(p^{nu+1}) alone
+// and, in the last pass of a cycle, p^k (which opens the next cycle) and the
+// iterate from the basis at once: nu + 4 vectors a pass and k + 3 a cycle,
+// against 2 nu + 6 and 2 with every p^l stored and summed.
+//
+// Cache hints: the basis vectors, the iterate and p^k are next touched a
+// whole step later or more (more than the Infinity Cache holds in between), so
 // they are loaded and stored with the non-temporal hint, leaving the cache
 // to e, r+ and L(p^{nu+1}), which the next passes read within the step.
 // NTAP extends the hint to the L(p^l) loads: set when the solve's k + 1
@@ -1666,10 +1714,11 @@ template <typename T, int KC, bool NTAP, int MESH>
 __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init)
 {
     __shared__ double sh[4];
-    __shared__ const T* s_p[KMAX + 1];
+    __shared__ const T* s_u[KMAX + 1];
     __shared__ const T* s_ap[KMAX + 1];
     __shared__ double s_al[KMAX + 1];
-    __shared__ double s_be[KMAX + 1];
+    __shared__ double s_pk[KMAX + 1];
+    __shared__ double s_xc[KMAX + 1];
     const int m = find_inst(tb.blk0_dir, tb.n, blockIdx.x);
     const Inst<T>& in = tb.inst[m];
     const int lb = blockIdx.x - tb.blk0_dir[m];
@@ -1677,31 +1726,29 @@ __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init
     if (st->status != RUNNING) return;
     if (!init && !st->active) return;
     const int nu = init ? -1 : st->nu;
-    const int target = st->slot[nu + 1];
-    const bool xupd = !init && (nu == st->k - 1);
-    const int xlo = st->x_base_nu;
-    T* pout = in.P[target];
-    T* apout = in.AP[target];
+    const bool last = !init && (nu == st->k - 1);
+    const T* ein = in.U[st->uslot[nu + 1]];
+    T* pout = in.U[st->uslot[last ? nu + 2 : 0]];
+    T* apout = in.AP[st->slot[nu + 1]];
     const T* rv = in.R[st->r_cur];
     const double* xb = in.X[st->x_base];
     double* xo = in.X[st->x_dst];
     if ((int)threadIdx.x <= nu) {
-        const int sl = st->slot[threadIdx.x];
-        s_p[threadIdx.x] = in.P[sl];
-        s_ap[threadIdx.x] = in.AP[sl];
+        s_u[threadIdx.x] = in.U[st->uslot[threadIdx.x]];
+        s_ap[threadIdx.x] = in.AP[st->slot[threadIdx.x]];
         s_al[threadIdx.x] = st->alpha[threadIdx.x];
-        s_be[threadIdx.x] = (xupd && (int)threadIdx.x >= xlo) ? st->beta[threadIdx.x] : 0.0;
+        s_pk[threadIdx.x] = last ? st->bm[nu + 1][threadIdx.x] : 0.0;
+        s_xc[threadIdx.x] = last ? st->xc[threadIdx.x] : 0.0;
     }
     __syncthreads();
     const StPos ps = st_pos_m<MESH>(in, lb, in.kc_dir, in.ord_dir);
     const int nz = in.g.nz;
     const long long plane = (long long)in.g.ncols;
     const long long c0 = (long long)ps.i + (long long)in.g.nx * ps.j;
-    double a[KC], p[KC], xa[KC], r[KC];
-    // p starts from e: the stencil's own centre values (no second load).
-    // On the octahedral mesh the step's dots pass has stored L(e): e and
-    // L(e) are loaded instead of gathering six neighbours again (the first
-    // direction of a solve or round, with no dots pass before it, forms it)
+    double a[KC], p[KC], r[KC];
+    // On the octahedral mesh the step's dots pass has stored L(e): it is
+    // loaded instead of gathering six neighbours again (the first direction
+    // of a solve or round, with no dots pass before it, forms it)
     bool formed = false;
     if constexpr (MESH == FTGCR_MESH_OCTAHEDRAL) {
         if (!init) {
@@ -1709,38 +1756,35 @@ __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init
             for (int kk = 0; kk < KC; ++kk) {
                 const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
                 const long long c = c0 + plane * kq;
-                p[kk] = (double)in.E[c];
+                p[kk] = last ? (double)ein[c] : 0.0;
                 a[kk] = (double)in.LE[c];
             }
             formed = true;
         }
     }
-    if (!formed) stencil_m<T, KC, MESH>(in.g, in.E, ps, a, p);
+    // p starts from e: the stencil's own centre values (no second load)
+    if (!formed) stencil_m<T, KC, MESH>(in.g, ein, ps, a, p);
     // r is needed only for the next beta's products at the end: binary32
     // loads it there (the registers it frees give that kernel a sixth wave
-    // per SIMD); FP64 loads it with the iterate (there a late load is
-    // slower, the occupancy being the same)
+    // per SIMD); FP64 loads it here (there a late load is slower, the
+    // occupancy being the same)
     constexpr bool R_LATE = sizeof(T) == 4;
 #pragma unroll
     for (int kk = 0; kk < KC; ++kk) {
         const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
-        const long long c = c0 + plane * kq;
-        if constexpr (!R_LATE) r[kk] = (double)rv[c];
-        xa[kk] = xupd ? __builtin_nontemporal_load(&xb[c]) : 0.0;
+        if constexpr (!R_LATE) r[kk] = (double)rv[c0 + plane * kq];
     }
     // sums over l in ascending order; term l + 1's loads are issued before
     // term l's values are used (two-stage pipeline, as in the dots pass)
     constexpr int PD = TERM_PIPE<T>;
-    T pb[PD][KC], ab[PD][KC];
+    T ab[PD][KC];
 #pragma unroll
     for (int l0 = 0; l0 < PD - 1; ++l0) {
         if (l0 <= nu) {
-            const gptr<T> pn = as_global(s_p[l0]);
             const gptr<T> apn = as_global(s_ap[l0]);
 #pragma unroll
             for (int kk = 0; kk < KC; ++kk) {
                 const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
-                pb[l0][kk] = __builtin_nontemporal_load(&pn[c0 + plane * kq]);
                 ab[l0][kk] = NTAP ? __builtin_nontemporal_load(&apn[c0 + plane * kq]) : apn[c0 + plane * kq];
             }
         }
@@ -1749,25 +1793,18 @@ __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init
     for (int l = 0; l < KMAX; ++l) {
         if (l <= nu) {
             const double al = s_al[l];
-            const double bl = s_be[l];
             const int ln = l + PD - 1;
             if (ln < KMAX && ln <= nu) {
-                const gptr<T> pn = as_global(s_p[ln]);
                 const gptr<T> apn = as_global(s_ap[ln]);
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk) {
                     const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
-                    pb[ln % PD][kk] = __builtin_nontemporal_load(&pn[c0 + plane * kq]);
                     ab[ln % PD][kk] = NTAP ? __builtin_nontemporal_load(&apn[c0 + plane * kq])
                                            : apn[c0 + plane * kq];
                 }
             }
 #pragma unroll
-            for (int kk = 0; kk < KC; ++kk) {
-                p[kk] = fma(al, (double)pb[l % PD][kk], p[kk]);
-                a[kk] = fma(al, (double)ab[l % PD][kk], a[kk]);
-                if (xupd) xa[kk] = fma(bl, (double)pb[l % PD][kk], xa[kk]);
-            }
+            for (int kk = 0; kk < KC; ++kk) a[kk] = fma(al, (double)ab[l % PD][kk], a[kk]);
         }
     }
     if constexpr (R_LATE) {
@@ -1781,18 +1818,51 @@ __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init
 #pragma unroll
     for (int kk = 0; kk < KC; ++kk) {
         const bool ok = ps.col_ok && ps.k0 + kk < nz;
-        const T ps_ = (T)p[kk];
         const T as_ = (T)a[kk];
-        if (ok) {
-            const long long c = c0 + plane * (ps.k0 + kk);
-            __builtin_nontemporal_store(ps_, &pout[c]);
-            apout[c] = as_;
-            if (xupd) __builtin_nontemporal_store(xa[kk], &xo[c]);
-        }
+        if (ok) apout[c0 + plane * (ps.k0 + kk)] = as_;
         const double ad = ok ? (double)as_ : 0.0;
         const double rd = ok ? r[kk] : 0.0;
         acc_num = fma(rd, ad, acc_num);
         acc_d = fma(ad, ad, acc_d);
+    }
+    if (last) {
+        // p^k and the iterate: sums over the basis in ascending order
+        double xa[KC];
+        T ub[2][KC];
+        const gptr<T> u0 = as_global(s_u[0]);
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk) {
+            const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
+            xa[kk] = __builtin_nontemporal_load(&xb[c0 + plane * kq]);
+            ub[0][kk] = __builtin_nontemporal_load(&u0[c0 + plane * kq]);
+        }
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) {
+            if (j <= nu) {
+                if (j + 1 < KMAX && j + 1 <= nu) {
+                    const gptr<T> un = as_global(s_u[j + 1]);
+#pragma unroll
+                    for (int kk = 0; kk < KC; ++kk) {
+                        const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
+                        ub[(j + 1) & 1][kk] = __builtin_nontemporal_load(&un[c0 + plane * kq]);
+                    }
+                }
+                const double pj = s_pk[j], xj = s_xc[j];
+#pragma unroll
+                for (int kk = 0; kk < KC; ++kk) {
+                    p[kk] = fma(pj, (double)ub[j & 1][kk], p[kk]);
+                    xa[kk] = fma(xj, (double)ub[j & 1][kk], xa[kk]);
+                }
+            }
+        }
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk) {
+            if (ps.col_ok && ps.k0 + kk < nz) {
+                const long long c = c0 + plane * (ps.k0 + kk);
+                __builtin_nontemporal_store((T)p[kk], &pout[c]);
+                __builtin_nontemporal_store(xa[kk], &xo[c]);
+            }
+        }
     }
     const double sn = block_sum(acc_num, sh);
     const double sd = block_sum(acc_d, sh);
@@ -1821,7 +1891,8 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_beta(Table<T> tb, int in
     state_word_store(gst, st);
 }
 
-// x = x_base + sum_{l = x_base_nu .. x_final_hi} beta_l p^l, into X[0].
+// x = x_base + sum_{l = x_base_nu .. x_final_hi} beta_l p^l (over the basis),
+// into X[0].
 template <typename T, int KC, int MESH>
 __global__ __launch_bounds__(ST_THREADS) void k_finalize_x(Table<T> tb)
 {
@@ -1831,6 +1902,13 @@ __global__ __launch_bounds__(ST_THREADS) void k_finalize_x(Table<T> tb)
     const SolveState* st = in.st;
     const int lo = st->x_base_nu, hi = st->x_final_hi;
     if (st->x_base == 0 && hi < lo) return;
+    __shared__ double s_c[KMAX + 1];
+    __shared__ const T* s_u[KMAX + 1];
+    if ((int)threadIdx.x <= hi) {
+        s_c[threadIdx.x] = basis_coef(st, threadIdx.x, lo, hi);
+        s_u[threadIdx.x] = in.U[st->uslot[threadIdx.x]];
+    }
+    __syncthreads();
     const StPos ps = st_pos_m<MESH>(in, lb, in.kc, in.ord_st);
     if (!ps.col_ok) return;
     const double* xb = in.X[st->x_base];
@@ -1840,7 +1918,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_finalize_x(Table<T> tb)
         if (ps.k0 + kk < in.g.nz) {
             const long long c = (long long)ps.i + (long long)in.g.nx * ps.j + (long long)in.g.ncols * (ps.k0 + kk);
             double xa = xb[c];
-            for (int l = lo; l <= hi; ++l) xa = fma(st->beta[l], (double)in.P[st->slot[l]][c], xa);
+            if (hi >= lo)
+                for (int j = 0; j <= hi; ++j) xa = fma(s_c[j], (double)as_global(s_u[j])[c], xa);
             xo[c] = xa;
         }
     }
@@ -1853,7 +1932,9 @@ __global__ __launch_bounds__(ST_THREADS) void k_finalize_x(Table<T> tb)
 // The working vectors share buffers with the backup where that is free
 // (the backup of p^0 / L(p^0) is the slot itself; x and r keep their
 // cycle-start buffer).  A flip must never reach the backup, so when the
-// current vector still is the backup's buffer it is first copied.
+// current vector still is the backup's buffer it is first copied.  A flip of
+// p^nu, nu > 0, first forms p^nu from the basis in the buffer of u_nu (which
+// no earlier direction contains): it takes u_nu's place in the basis.
 
 template <typename T>
 __global__ void k_event_prep(Table<T> tb, int vec)
@@ -1898,6 +1979,13 @@ __global__ void k_event_prep(Table<T> tb, int vec)
             st->ev_copy = 1;
             st->slot[0] = dst;
             st->slot[1] = src;
+            const int last = st->k + 1;
+            st->ev_usrc = st->uslot[0];
+            st->ev_udst = st->uslot[last];
+            st->uslot[0] = st->ev_udst;
+            st->uslot[last] = st->ev_usrc;
+        } else if (nu > 0 && vec == FTGCR_V_P) {
+            st->ev_copy = 2;
         }
     }
 }
@@ -1910,17 +1998,30 @@ __global__ void k_event_copy(Table<T> tb)
     if (!st->ev_ok || !st->ev_copy) return;
     const long long n = in.g.n;
     const int vec = st->ev_vec;
+    const int nu = st->nu;
+    __shared__ double s_c[KMAX + 1];
+    if ((int)threadIdx.x <= KMAX) {
+        const int j = threadIdx.x;
+        s_c[j] = vec == FTGCR_V_X ? basis_coef(st, j, st->ev_lo, st->ev_hi - 1)
+                 : (st->ev_copy == 2 && j <= nu) ? st->bm[nu][j] : 0.0;
+    }
+    __syncthreads();
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n; c += stride) {
         if (vec == FTGCR_V_X) {
             double xa = in.X[st->ev_src][c];
-            for (int l = st->ev_lo; l < st->ev_hi; ++l)
-                xa = fma(st->beta[l], (double)in.P[st->slot[l]][c], xa);
+            if (st->ev_hi > st->ev_lo)
+                for (int j = 0; j < st->ev_hi; ++j) xa = fma(s_c[j], (double)in.U[st->uslot[j]][c], xa);
             in.X[st->ev_dst][c] = xa;
         } else if (vec == FTGCR_V_R) {
             in.R[st->ev_dst][c] = in.R[st->ev_src][c];
+        } else if (st->ev_copy == 2) {
+            T* u = in.U[st->uslot[nu]];
+            double pa = (double)u[c];
+            for (int j = 0; j < nu; ++j) pa = fma(s_c[j], (double)in.U[st->uslot[j]][c], pa);
+            u[c] = (T)pa;
         } else {
-            in.P[st->ev_dst][c] = in.P[st->ev_src][c];
+            in.U[st->ev_udst][c] = in.U[st->ev_usrc][c];
             in.AP[st->ev_dst][c] = in.AP[st->ev_src][c];
         }
     }
@@ -1940,13 +2041,15 @@ __global__ void k_event_inject(Table<T> tb, const long long* idx, const unsigned
         const int bit = bits ? (int)bits[t] : bit0;
         if (vec == FTGCR_V_X) write_xor<double>(in.X[st->x_base] + at, bit);
         else if (vec == FTGCR_V_R) write_xor<T>(in.R[st->r_cur] + at, bit);
-        else if (vec == FTGCR_V_P) write_xor<T>(in.P[st->slot[st->nu]] + at, bit);
+        else if (vec == FTGCR_V_P) write_xor<T>(in.U[st->uslot[st->nu]] + at, bit);
         else if (vec == FTGCR_V_AP) write_xor<T>(in.AP[st->slot[st->nu]] + at, bit);
-        else write_xor<T>(in.E + at, bit);
+        else write_xor<T>(in.U[st->uslot[st->nu + 1]] + at, bit);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st->events_applied += 1;
         st->events_since_rb = 1;
+        if (vec == FTGCR_V_P && st->ev_copy == 2)   // the basis holds p^nu itself now
+            for (int j = 0; j < st->nu; ++j) st->bm[st->nu][j] = 0.0;
     }
 }
 
