@@ -116,14 +116,19 @@ typedef struct {
     int32_t inner_max_steps; /* MIXED: cap on inner steps per round            */
     int64_t hist_cap;        /* entries of the per-step residual history kept   */
     int32_t use_graphs;      /* 1: replay captured step sequences (hipGraph)     */
-    int32_t levels_per_block;/* stencil kernels: levels per block (0 = auto)    */
+    int32_t levels_per_block;/* stencil kernels: levels per block (0 = auto;
+                                grids that fit the GPU's registers then run
+                                many steps in one cooperative launch, which
+                                any explicit tiling or block order rules out) */
     int32_t profile_kernels; /* time step kernels with a HIP event pair each,
                                 stamped by the kernel's own dispatch on the
                                 solve stream (ftgcr_kernel_times).  Bits 0-7:
                                 0 off, 1 all three, else a mask of bit 1
                                 update_thomas, bit 2 stencil_dots, bit 3
                                 dir_update; bits 8-15: a stride s > 1 times
-                                only steps whose number is a multiple of s   */
+                                only steps whose number is a multiple of s.
+                                Where many steps run in one launch, its
+                                three passes as clocked on the device          */
     int32_t batch_levels_per_block; /* ftgcr_solve_batch with this handle as
                                 the first member: stencil levels per block of
                                 the combined launches (1, 2, 4, 8 or 16; 0 =

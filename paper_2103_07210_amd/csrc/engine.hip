@@ -64,7 +64,7 @@ struct ftgcr_handle {
     SolveState* st = nullptr;       // device control state
     void* inst = nullptr;           // device Inst<T> of the storage type
     Inst<double>* inst_dbg = nullptr;  // device Inst<double> for the parity entry points
-    int* blk0 = nullptr;            // device {0, nblk_col, 0, nblk_st, 0, nblk_dir}
+    int* blk0 = nullptr;            // device {0, nblk_col, 0, nblk_st, 0, nblk_dir, 0, nblk_res}
     SolveState* st_host = nullptr;  // pinned copy for reading back
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
 
@@ -81,6 +81,11 @@ struct ftgcr_handle {
     int graph_steps = 0;
     bool graph_nt_ap = false;
     bool nt_ap = false;   // this solve's L(p^l) load hint (nt_ap_hint)
+
+    // the resident kernel's shape (res_waves 0: this grid does not take it) and
+    // exchange words (device)
+    int res_waves = 0, nblk_res = 0, rtx = 0;
+    unsigned long long* xw = nullptr;
 
     int nblk_col = 0, nblk_st = 0, nblk_dir = 0;
     int kc = 1, tx = 1, ty = 1, tz = 1, H = 4, kc_dir = 1, tz_dir = 1;
@@ -293,8 +298,51 @@ Inst<T> make_inst(const ftgcr_handle* h, const double* rhs, double* x, void* ws)
     in.tz_dir = h->tz_dir;
     in.ord_st = h->ord_st;
     in.ord_dir = h->ord_dir;
+    in.xw = h->xw;
+    in.nblk_res = h->nblk_res;
+    in.rtx = h->rtx;
     return in;
 }
+
+// Decide whether solves of this handle run in the resident kernel, and give
+// it its exchange words.  A grid it does not take, or a device without
+// cooperative launches, leaves the handle to the streaming kernels.
+ftgcr_status setup_resident(ftgcr_handle* h)
+{
+    if (h->precond != FTGCR_PRECOND_COLUMN) return FTGCR_OK;
+    const bool mixed = h->precision == FTGCR_MIXED;
+    const Geo& g = h->geo;
+    int cus = 0;
+    HIP_TRY(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device));
+    const int w = resident_waves(g.mesh, g.nx, g.ny, h->H, mixed ? 4 : 8, cus, &h->rtx, &h->nblk_res);
+    if (w == 0 || !(mixed ? resident_fits<float>(g.mesh, h->H, w, h->nblk_res, h->kmax)
+                          : resident_fits<double>(g.mesh, h->H, w, h->nblk_res, h->kmax)))
+        return FTGCR_OK;
+    HIP_TRY(h, hipMalloc(&h->xw, RES_WORDS * sizeof(unsigned long long)));
+    HIP_TRY(h, hipMemset(h->xw, 0, RES_WORDS * sizeof(unsigned long long)));
+    h->res_waves = w;
+    return FTGCR_OK;
+}
+
+// A tiling asked for in the options means the streaming kernels.
+bool use_resident(const ftgcr_handle* h)
+{
+    return h->res_waves > 0 && h->opt.levels_per_block == 0 && h->opt.order_stencil == FTGCR_ORDER_AUTO &&
+           h->opt.order_dir == FTGCR_ORDER_AUTO;
+}
+
+// options.profile_kernels, bits 0-7: 1 times all three step kernels, any
+// other nonzero value is a mask (bit 1 update_thomas, bit 2 stencil_dots, bit 3
+// dir_update); bits 8-15: a stride s > 1 times only the steps whose number is
+// a multiple of s (for s coprime with k the sample covers every pass index
+// alike).
+int profile_mask(const ftgcr_handle* h)
+{
+    const int sel = h->opt.profile_kernels & 0xFF;
+    return sel == 1 ? 0xE : sel;
+}
+
+int profile_stride(const ftgcr_handle* h) { return (h->opt.profile_kernels >> 8) & 0xFF; }
 
 ftgcr_status upload_tables(ftgcr_handle* h)
 {
@@ -565,7 +613,7 @@ ftgcr_status upload_debug_inst(ftgcr_handle* h)
     in.ord_st = h->ord_st;
     in.ord_dir = h->ord_dir;
     HIP_TRY(h, hipMemcpy(h->inst_dbg, &in, sizeof in, hipMemcpyHostToDevice));
-    const int blk0[6] = {0, h->nblk_col, 0, h->nblk_st, 0, h->nblk_dir};
+    const int blk0[8] = {0, h->nblk_col, 0, h->nblk_st, 0, h->nblk_dir, 0, h->nblk_res};
     HIP_TRY(h, hipMemcpy(h->blk0, blk0, sizeof blk0, hipMemcpyHostToDevice));
     return FTGCR_OK;
 }
@@ -581,6 +629,9 @@ struct DevEvent {
     const long long* idx;        // device or null
     const unsigned char* bits;   // device or null
 };
+
+// Steps a resident launch runs at most before the host looks at the state.
+constexpr long long RES_STEPS = 4096;
 
 const char* const kKernelNames[3] = {"update_thomas", "stencil_dots", "dir_update"};
 
@@ -626,14 +677,8 @@ struct Runner {
     template <class F>
     void timed(int cls, F&& launch)
     {
-        // profile_kernels, bits 0-7: 1 times all three step kernels, any
-        // other nonzero value is a mask (bit 1 update_thomas, bit 2
-        // stencil_dots, bit 3 dir_update); bits 8-15: a stride s > 1 times
-        // only the steps whose number is a multiple of s (for s coprime with
-        // k the sample covers every pass index alike)
-        const int sel = noalloc ? 0 : (h->opt.profile_kernels & 0xFF);
-        const int stride = (h->opt.profile_kernels >> 8) & 0xFF;
-        const int mask = sel == 1 ? 0xE : sel;
+        const int mask = noalloc ? 0 : profile_mask(h);
+        const int stride = profile_stride(h);
         if (!(mask & (2 << cls)) || (stride > 1 && cur_step % stride != 0)) {
             launch(nullptr, nullptr);
             return;
@@ -742,11 +787,11 @@ struct Runner {
 
     // Enqueue steps until the device reports an outcome.  `launched` is the
     // number of steps executed so far (the device's s).
-    ftgcr_status run_steps(long long launched, long long cap, const std::vector<DevEvent>& evs)
+    ftgcr_status run_steps(int k, long long launched, long long cap, const std::vector<DevEvent>& evs)
     {
         size_t evp = 0;
         const int chunk = std::max(1, h->opt.poll_steps);
-        const long long guard = cap + chunk + 16;
+        const long long guard = cap + std::max<long long>(chunk, RES_STEPS) + 16;
         long long issued = 0;
         // Chunks after the first are sized from the observed convergence
         // rate: steps past the exit are launched and return at once, so the
@@ -755,9 +800,24 @@ struct Runner {
         long long want = chunk;
         double rr_prev = -1.0;
         long long s_prev = 0;
+        bool resident_norms = false;   // the state's norms are the resident kernel's
         while (true) {
             while (evp < evs.size() && evs[evp].step <= launched) ++evp;
-            if (evp < evs.size() && evs[evp].step == launched + 1) {
+            const bool event_now = evp < evs.size() && evs[evp].step == launched + 1;
+            bool resident = use_resident(h);
+            if (event_now && resident) {
+                // events at the start of a step come between two launches of
+                // the resident kernel; one inside a step (e), or one on r
+                // while the state's norms are the streaming kernels', leaves
+                // that step to the streaming kernels
+                for (size_t q = evp; q < evs.size() && evs[q].step == launched + 1; ++q)
+                    if (evs[q].vec == FTGCR_V_E || (evs[q].vec == FTGCR_V_R && !resident_norms)) resident = false;
+            }
+            if (resident_norms && !resident) {
+                L::norms(tb, h->nblk_col, h->H, s);
+                resident_norms = false;
+            }
+            if (event_now && !resident) {
                 std::vector<const DevEvent*> mid;
                 for (; evp < evs.size() && evs[evp].step == launched + 1; ++evp) {
                     if (evs[evp].vec == FTGCR_V_E) mid.push_back(&evs[evp]);
@@ -766,6 +826,23 @@ struct Runner {
                 step(launched + 1, &mid);
                 launched += 1;
                 issued += 1;
+            } else if (resident) {
+                for (; evp < evs.size() && evs[evp].step == launched + 1; ++evp) event(evs[evp]);
+                // to the next event or the outcome, in one launch
+                long long cnt = RES_STEPS;
+                if (evp < evs.size()) cnt = std::min<long long>(cnt, evs[evp].step - 1 - launched);
+                const ResidentArgs arg{launched + cnt, k + 1, resident_norms ? 0 : 1, noalloc ? 0 : profile_mask(h),
+                                       profile_stride(h)};
+                const hipError_t e =
+                    resident_run<T>(tb, h->blk0 + 6, h->nblk_res, h->geo.mesh, h->H, h->res_waves, arg, s);
+                if (e != hipSuccess) {   // the device does not take the launch: the streaming kernels from here
+                    (void)hipGetLastError();
+                    h->res_waves = 0;
+                    continue;
+                }
+                resident_norms = true;
+                launched += cnt;
+                issued += cnt;
             } else {
                 long long cnt = want;
                 if (evp < evs.size()) cnt = std::min<long long>(cnt, evs[evp].step - 1 - launched);
@@ -782,6 +859,13 @@ struct Runner {
             int status = RUNNING;
             ftgcr_status rc = read_status(&status);
             if (rc != FTGCR_OK) return rc;
+            if (resident) {
+                for (int q = 0; q < 3; ++q) {
+                    h->kt_ms[q] += 1e-5 * (double)h->st_host->res_ticks[q];
+                    h->kt_n[q] += h->st_host->res_counts[q];
+                }
+            }
+            if (h->st_host->res_fail) return fail(h, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
             if (status != RUNNING) return FTGCR_OK;
             if (issued > guard) return fail(h, FTGCR_E_HIP, "step loop did not terminate");
             const SolveState& hs = *h->st_host;
@@ -937,7 +1021,7 @@ ftgcr_status solve_impl(ftgcr_handle* h, const double* rhs, double* x, double to
         L::init_state(tb, k, h->opt.ft, 0, max_steps, tol * tol, 1, 1, s);
         L::residual(tb, h->nblk_st, h->kc, 1, 1, s);
         run.start_round();
-        rc = run.run_steps(0, max_steps, evs);
+        rc = run.run_steps(k, 0, max_steps, evs);
         if (rc != FTGCR_OK) return rc;
         L::finalize_x(tb, h->nblk_st, h->kc, s);
     } else {
@@ -965,7 +1049,7 @@ ftgcr_status solve_impl(ftgcr_handle* h, const double* rhs, double* x, double to
             L::set_round(tb, tau * tau, cap, s);
             if (!run.noalloc) roctxRangePushA("ftgcr refinement round");
             run.start_round();
-            rc = run.run_steps(s0, cap, evs);
+            rc = run.run_steps(k, s0, cap, evs);
             if (!run.noalloc) roctxRangePop();
             if (rc != FTGCR_OK) return rc;
             L::finalize_x(tb, h->nblk_st, h->kc, s);
@@ -1550,11 +1634,13 @@ ftgcr_status ftgcr_create(const ftgcr_grid* grid, const ftgcr_coeffs* coeffs, ft
     if (rc != FTGCR_OK) return bail(rc);
     h->H = thomas_depth(grid->nz);
     set_tiling(h);
+    rc = setup_resident(h);
+    if (rc != FTGCR_OK) return bail(rc);
     if (hipMalloc(&h->st, sizeof(SolveState)) != hipSuccess ||
         hipMemset(h->st, 0, sizeof(SolveState)) != hipSuccess ||
         hipMalloc(&h->inst, std::max(sizeof(Inst<double>), sizeof(Inst<float>))) != hipSuccess ||
         hipMalloc(&h->inst_dbg, sizeof(Inst<double>)) != hipSuccess ||
-        hipMalloc(&h->blk0, 6 * sizeof(int)) != hipSuccess ||
+        hipMalloc(&h->blk0, 8 * sizeof(int)) != hipSuccess ||
         hipHostMalloc(&h->st_host, sizeof(SolveState)) != hipSuccess ||
         hipMalloc(&h->gm_st, sizeof(GmState)) != hipSuccess || hipMalloc(&h->gm_inst, sizeof(GmInst)) != hipSuccess ||
         hipHostMalloc(&h->gm_host, sizeof(GmState)) != hipSuccess ||
@@ -1925,6 +2011,7 @@ void ftgcr_destroy(ftgcr_handle* h)
     if (h->inst) (void)hipFree(h->inst);
     if (h->inst_dbg) (void)hipFree(h->inst_dbg);
     if (h->blk0) (void)hipFree(h->blk0);
+    if (h->xw) (void)hipFree(h->xw);
     if (h->st_host) (void)hipHostFree(h->st_host);
     if (h->ev_start) (void)hipEventDestroy(h->ev_start);
     if (h->ev_stop) (void)hipEventDestroy(h->ev_stop);

@@ -61,6 +61,10 @@ struct DetectRec {
 // Per-solve control state (device memory, written by single-thread kernel
 // sections only).
 struct SolveState {
+    int res_fail;        // 1: a resident kernel's block waited in vain (never stored back from a copy)
+    unsigned res_seq;    // rounds of exchanges the resident kernels of this handle have run
+    unsigned long long res_ticks[3];   // the last resident launch's timed rounds (100 MHz)
+    int res_counts[3], res_pad;
     int status;          // RUNNING or an FTGCR_* outcome
     int active;          // 1: this step goes on to P^{-1}, L and the new direction
     int nu;              // pass index of the current step
@@ -178,6 +182,9 @@ struct Inst {
     int nblk_dir, kc_dir, tz_dir;
     // block orders (ORD_*) of the stencil grid and of the direction grid
     int ord_st, ord_dir;
+    // the resident kernel's exchange words, blocks and tiles in x
+    unsigned long long* xw;
+    int nblk_res, rtx;
 };
 
 // FT-GMRES(k) control state of one solve (device memory; written by single
@@ -248,6 +255,38 @@ inline bool full_columns(long long ncols, int nz, int H)
     return nz == 2 * H && ncols % COLS_PER_BLOCK == 0;
 }
 
+// The resident kernel (resident.hip): whole columns kept in registers by
+// blocks that stay on the GPU for many steps.  RES_COLS columns per wavefront
+// (two lanes each), at most RES_WAVES wavefronts per block, at most
+// RES_BLOCKS blocks.
+constexpr int RES_COLS = 32;
+constexpr int RES_WAVES = 8;
+constexpr int RES_BLOCKS = 256;
+// exchange words of a handle: two rounds in turn, each in RES_COPIES copies
+// (every block writes all and reads one, so fewer blocks poll the same
+// memory: 2.8 -> 2.5 us a round on 256 blocks), NV_MAX values per block, two
+// tagged words a value
+constexpr int RES_COPIES = 4;
+constexpr size_t RES_WORDS = 2 * (size_t)RES_COPIES * NV_MAX * RES_BLOCKS * 2;
+
+// Wavefronts per block with which the resident kernel takes a problem of
+// half columns of depth H on at most `cus` blocks (0: it does not), and its
+// tile counts.
+int resident_waves(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int* rtx, int* nblk);
+// Whether the device can hold the kernel's blocks all at once.
+template <typename T> bool resident_fits(int mesh, int H, int waves, int nblk, int k);
+// What a launch runs: steps until every instance has left RUNNING or executed
+// s_stop of them.
+struct ResidentArgs {
+    long long s_stop;
+    int nvmax;         // k + 1: the most sums in a round
+    int new_norms;     // 1: form the state's norms of r anew first
+    int time_mask, time_stride;   // options.profile_kernels
+};
+template <typename T>
+hipError_t resident_run(const Table<T>& tb, const int* blk0, int total_blocks, int mesh, int H, int waves,
+                        ResidentArgs arg, hipStream_t s);
+
 // Kernel launchers (kernels.hip).
 template <typename T> struct Launch {
     static void init_state(const Table<T>& tb, int k, int ft, int mixed, long long max_steps, double tol2,
@@ -259,6 +298,8 @@ template <typename T> struct Launch {
     static void update_thomas(const Table<T>& tb, int total_col_blocks, int H, int mode, hipStream_t s,
                               hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
     static void finish_col(const Table<T>& tb, int mode, hipStream_t s);
+    // the state's norms in the column pass's order (single instance)
+    static void norms(const Table<T>& tb, int total_col_blocks, int H, hipStream_t s);
     // spec = 1: before the step's decision, followed by finish_step
     static void stencil_dots(const Table<T>& tb, int total_st_blocks, int kc, int spec, hipStream_t s,
                              hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
