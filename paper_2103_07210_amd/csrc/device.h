@@ -48,6 +48,15 @@ __device__ __forceinline__ gptr_mut<T> as_global_mut(T* p)
     return (gptr_mut<T>)p;
 }
 
+// The value is formed here: its arithmetic is not moved to where it is used
+// (which would keep all operands instead of the result), and what follows from
+// it is not formed once before the step loop (and kept).
+template <typename V>
+__device__ __forceinline__ void settle(V& v)
+{
+    asm volatile("" : "+v"(v));
+}
+
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov_f64(double v)
 {

@@ -1006,8 +1006,7 @@ ftgcr_status solve_impl(ftgcr_handle* h, const double* rhs, double* x, double to
     HIP_TRY(h, hipMemcpyAsync(h->inst, &in, sizeof in, hipMemcpyHostToDevice, s));
     HIP_TRY(h, hipStreamSynchronize(s));
     Runner<T> run{h,
-                  Table<T>{(const Inst<T>*)h->inst, h->blk0, h->blk0 + 2, h->blk0 + 4, 1, h->geo.mesh, h->precond,
-                           full_columns(h->geo.ncols, h->geo.nz, h->H) ? 1 : 0},
+                  Table<T>{(const Inst<T>*)h->inst, h->blk0, h->blk0 + 2, h->blk0 + 4, 1, h->geo.mesh, h->precond},
                   s};
     run.noalloc = staging != nullptr;
     const Table<T>& tb = run.tb;
@@ -1132,8 +1131,7 @@ ftgcr_status gm_solve_impl(ftgcr_handle* h, const double* rhs, double* x, double
     HIP_TRY(h, hipStreamSynchronize(s));
     const GmInst* d = h->gm_inst;
     // geometry and the column grid of the two-lane FP64 column kernel
-    const Table<double> tb{h->inst_dbg, h->blk0, h->blk0 + 2, h->blk0 + 4, 1, h->geo.mesh, h->precond,
-                           full_columns(h->geo.ncols, h->geo.nz, h->H) ? 1 : 0};
+    const Table<double> tb{h->inst_dbg, h->blk0, h->blk0 + 2, h->blk0 + 4, 1, h->geo.mesh, h->precond};
     const int nblk_col = (h->geo.ncols + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
     const int nst = h->nblk_st, kc = h->kc;
     GmState* hs = h->gm_host;
@@ -1302,10 +1300,10 @@ ftgcr_status upload_batch(ftgcr_handle* h0, const std::vector<Inst<double>>& ins
     const int na = (int)members.size();
     std::vector<Inst<double>> act(na);
     std::vector<int> pre(3 * (na + 1), 0);
-    bool full = true;
+    bool mixed_depth = false;
     for (int q = 0; q < na; ++q) {
         act[q] = ins[members[q]];
-        full = full && full_columns(act[q].g.ncols, act[q].g.nz, H);
+        mixed_depth = mixed_depth || thomas_depth(act[q].g.nz) != H;
         pre[q + 1] = pre[q] + act[q].nblk_col;
         pre[na + 1 + q + 1] = pre[na + 1 + q] + act[q].nblk_st;
         pre[2 * (na + 1) + q + 1] = pre[2 * (na + 1) + q] + act[q].nblk_dir;
@@ -1317,7 +1315,7 @@ ftgcr_status upload_batch(ftgcr_handle* h0, const std::vector<Inst<double>>& ins
     sh.sts = pre[2 * na + 1];
     sh.dirs = pre[3 * na + 2];
     tb = Table<double>{inst, blk0, blk0 + na + 1, blk0 + 2 * (na + 1), na, h0->geo.mesh, h0->precond,
-                       full ? 1 : 0};
+                       mixed_depth ? 1 : 0};
     return FTGCR_OK;
 }
 

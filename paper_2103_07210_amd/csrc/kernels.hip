@@ -539,18 +539,35 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_residual(Table<T> tb, in
 //
 // Each column (i, j) is split between two lanes of a wave (lane l and l+32):
 // the lower lane eliminates levels 0 .. h-1 upward (Thomas forward sweep),
-// the upper lane levels nz-1 .. h downward; they meet at row h-1, exchange
+// the upper lane levels nz-1 .. h downward; they meet at level h-1, exchange
 // one pivot pair by a lane shuffle, and each back-substitutes its half.  The
 // elimination state of a half column (at most H levels) stays in registers.
 // P's rows: a_k e_{k-1} + b_k e_k + u_k e_{k+1} = r_k with b the diagonal of
-// A and a, u minus the vertical face weights.  All loads of a half column are
-// issued before its first store (r is updated in place after the first pass
-// of a cycle, so program order must not interleave them).
+// A and a, u minus the vertical face weights.
+//
+// A lane's rows run from its outer end to the middle: row H - 1 is level h - 1
+// (lower) or h (upper), so where the halves meet, and every row after the
+// first pad_rows(H), is the same in every column, and only those first rows
+// are guarded.  Behind a guard on each row's store of r+ the compiler moved
+// every row's elimination after all the stores, and a column that did not
+// fill its template exactly ran at one or two waves per SIMD with all rows'
+// values in registers; settle() keeps a row's results formed beside its
+// loads.  The empty rows (levels a half is short of H) read the outermost
+// level's address, take no part in the sums and store nothing.
+
+// Most empty rows of a half column in the template of depth H (the next
+// smaller depth holds anything shorter).
+constexpr int pad_rows(int H)
+{
+    return H == 4 ? 4 : H == 8 ? 5 : H == 16 ? 9 : H == 24 ? 9 : H == 28 ? 5 : H == 32 ? 5 : 9;
+}
 
 // MODE_GM (FT-GMRES, FP64): the current Arnoldi vector U[j] is divided by
 // den[j] (normalised, written back in place) and z_j = P^{-1} v_j goes to
 // Z[j]; no norms.
-template <typename T, int H, int mode, bool FULL>
+// ANY: the launch's columns may be shorter than the template's range (a batch
+// of members of different depths), so every row is guarded.
+template <typename T, int H, int mode, bool ANY>
 __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in, T* dbg_out, const GmInst* gm)
 {
     // The column solve runs in the storage precision: FP64 for FP64 solves;
@@ -559,14 +576,17 @@ __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in,
     // update r+ = r + beta L(p) and both norms stay FP64.
     using CT = T;
     __shared__ double sh[4];
-    __shared__ CT s_gc[2 * H];
-    __shared__ CT s_gf[2 * H + 1];
+    // per half and row: the vertical decay at the level, and at the face
+    // towards the middle with a 1 (both 0 at the bottom and top faces and in
+    // empty rows)
+    __shared__ CT s_lev[2][H], s_face[2][H][2];
     // Half columns longer than 32 levels: the multipliers of the first LH
     // rows (the last ones the back-substitution reads) wait in LDS, the rest
     // in registers, so that the kernel fits two waves per SIMD (all 48
     // levels in registers take about 370 registers in FP64: one wave)
     constexpr int LH = H > 32 ? (sizeof(CT) == 8 ? 19 : 16) : 0;
     constexpr int RH = H - LH;
+    constexpr int PAD = ANY ? H : pad_rows(H);
     __shared__ CT s_stk[LH > 0 ? LH : 1][2][COL_THREADS];
     const int m = find_inst(tb.blk0_col, tb.n, blockIdx.x);
     const Inst<T>& in = tb.inst[m];
@@ -583,10 +603,18 @@ __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in,
     // before the first store, so no later access can wait behind a store
     const Geo& g = in.g;
     const int nx = g.nx, nz = g.nz, ncols = g.ncols;
+    const int h = (nz + 1) >> 1;   // lower half: levels [0, h), upper half: [h, nz)
     const double opsig = g.opsig;
     // vertical decay tables in LDS (LDS reads do not queue behind stores)
-    for (int t = threadIdx.x; t < nz; t += blockDim.x) s_gc[t] = (CT)g.gc[t];
-    for (int t = threadIdx.x; t <= nz; t += blockDim.x) s_gf[t] = (CT)g.gf[t];
+    for (int t = threadIdx.x; t < 2 * H; t += blockDim.x) {
+        const int up = t / H, q = t % H;
+        const int a = q - (H - (up ? nz - h : h));   // levels from the outer end
+        const int k = up ? nz - 1 - a : a, f = up ? k : k + 1;
+        const bool inner = a >= 0 && f > 0 && f < nz;
+        s_lev[up][q] = a >= 0 ? (CT)g.gc[k] : CT(0);
+        s_face[up][q][0] = inner ? (CT)g.gf[f] : CT(0);
+        s_face[up][q][1] = inner ? CT(1) : CT(0);
+    }
     const CT opsig_c = (CT)opsig;
     const T* rin;
     const T* ap;
@@ -622,167 +650,134 @@ __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in,
     __syncthreads();
 
     const int lane = threadIdx.x & 63;
-    const bool upper = lane >= 32;
+    const int upper = lane >> 5;
     const int col = lb * COLS_PER_BLOCK + (threadIdx.x >> 6) * 32 + (lane & 31);
-    const bool valid = col < ncols;
-    const int colc = valid ? col : 0;
-    const int j = colc / nx;
-    const int i = colc - j * nx;
-    const long long plane = (long long)ncols;
-    const int h = (nz + 1) >> 1;   // lower half: levels [0, h)
-    const int nup = nz - h;        // upper half: levels [h, nz)
-    const int nmine = upper ? nup : h;
-    // diagonal h0 + g_k h1 + vertical faces, from the same per-column
-    // constants and in the same order as the stencil rows (identical)
-    const typename RowOf<CT>::type rcst = col_consts_for<CT>(g, i, j);
-    const CT h0 = rcst.h0;
-    const CT h1 = rcst.h1;
-    const CT gz = rcst.gz, hc = rcst.hc;
-
-    // The half column streams in chunks of CH levels, each chunk's loads
-    // issued one chunk ahead of its elimination (a two-stage software
-    // pipeline): loads are branch-free (clamped addresses, results
-    // selected), so a chunk's loads are all in flight together, and they are
-    // issued before the previous chunk's stores, so waiting for them never
-    // waits for a store.  The elimination is the same instruction stream
-    // for both halves: the lower lane eliminates towards level 0 (near
-    // coupling a_k, far coupling u_k), the upper lane towards nz-1 (near
-    // u_k, far a_k).
-    // r is loaded with the non-temporal hint: this is its last use in the
-    // step (the direction pass reads r+), and the hint leaves the Infinity
-    // Cache to what the next passes re-read (e, r+, the L(p^l)).
-    // FP64 streams in 4-level chunks: with 8 the half column's registers
-    // exceed 256 and the kernel drops to one wave per SIMD.  binary32 values
-    // are half the bytes per load, so it streams 16 levels ahead where the
-    // half column allows (more bytes in flight per wave)
-    constexpr int CHW = sizeof(T) == 8 ? 4 : (H % 16 == 0 ? 16 : (H % 8 == 0 ? 8 : 4));
-    constexpr int CH = H < CHW ? H : CHW;
-    constexpr int NCH = H / CH;
-    static_assert(H % CH == 0, "chunks must tile the half column");
-    T bufr[2][CH], bufa[2][CH];
-    CT de[RH], ga[RH];
     double acc_new = 0.0, acc_st = 0.0;
-    CT carry_g = 0, carry_d = 0;
-    CT mm = 1, ff = 0, uu = 0;   // meeting row of the lower lane
-    CT w_near = 0;                // face below level 0 / above level nz-1
-    // r+ is stored through a pointer that walks one level per row (a fresh
-    // induction value, so the loads' 64-bit addresses need not stay live)
-    const long long wstep = upper ? -plane : plane;
-    gptr_mut<T> rw = as_global_mut((mode == MODE_STEP || mode == MODE_GM) ? rout : eout) + (long long)colc +
-                     plane * (upper ? nz - 1 : 0);
-    asm volatile("" : "+v"(rw));
+    if (col < ncols) {   // (both lanes of a column or neither)
+        const int j = col / nx;
+        const int i = col - j * nx;
+        const long long plane = (long long)ncols;
+        const int nmine = upper ? nz - h : h;
+        const int pad = H - nmine;
+        // diagonal h0 + g_k h1 + vertical faces, from the same per-column
+        // constants and in the same order as the stencil rows (identical)
+        const typename RowOf<CT>::type rcst = col_consts_for<CT>(g, i, j);
+        const CT h0 = rcst.h0;
+        const CT h1 = rcst.h1;
+        const CT gz = rcst.gz, hc = rcst.hc;
+        auto face = [&](int q) -> CT { return gz * fma(hc, s_face[upper][q][0], s_face[upper][q][1]); };
+
+        // The half column streams in chunks of CH levels, each chunk's loads
+        // issued one chunk ahead of its elimination (a two-stage software
+        // pipeline), before the previous chunk's stores, so waiting for them
+        // never waits for a store.  The elimination is the same instruction
+        // stream for both halves.
+        // r is loaded with the non-temporal hint: this is its last use in the
+        // step (the direction pass reads r+), and the hint leaves the Infinity
+        // Cache to what the next passes re-read (e, r+, the L(p^l)).
+        // FP64 streams in 4-level chunks: with 8 the half column's registers
+        // exceed 256 and the kernel drops to one wave per SIMD.  binary32 values
+        // are half the bytes per load, so it streams 16 levels ahead where the
+        // half column allows (more bytes in flight per wave)
+        constexpr int CHW = sizeof(T) == 8 ? 4 : (H % 16 == 0 ? 16 : (H % 8 == 0 ? 8 : 4));
+        constexpr int CH = H < CHW ? H : CHW;
+        constexpr int NCH = H / CH;
+        static_assert(H % CH == 0, "chunks must tile the half column");
+        T bufr[2][CH], bufa[2][CH];
+        CT de[RH], ga[RH];
+        CT carry_g = 0, carry_d = 0;
+        CT w_out = 0;                // face towards the column's end (0 at the bottom and top)
+        CT mk = 1, fk = 0;
+        // offsets walk one level per row (a fresh induction value, so no row's
+        // 64-bit address need stay live), from the outermost level; a half
+        // without rows (one level) stays on level 0
+        const long long step = upper ? -plane : plane;
+        const long long first = (long long)col + (upper && nmine > 0 ? plane * (nz - 1) : 0);
+        const int walk = nmine > 0 ? pad : H;   // rows before this one do not move
+        gptr<T> rp = as_global(rin) + first;
+        gptr<T> app = as_global(ap) + first;
+        gptr_mut<T> rw = as_global_mut((mode == MODE_STEP || mode == MODE_GM) ? rout : eout) + first;
+        asm volatile("" : "+v"(rp), "+v"(app), "+v"(rw));
+        auto load = [&](int q, T& rv, T& av) {
+            rv = __builtin_nontemporal_load(rp);
+            av = (mode == MODE_STEP) ? *app : T(0);
+            const long long d = (q < PAD && q < walk) ? 0 : step;
+            if (q + 1 < H) {
+                rp += d;
+                app += d;
+            }
+        };
 #pragma unroll
-    for (int t = 0; t < CH; ++t) {
-        int k = upper ? nz - 1 - t : t;
-        k = k < 0 ? 0 : (k > nz - 1 ? nz - 1 : k);
-        const long long o = (long long)colc + plane * k;
-        bufr[0][t] = __builtin_nontemporal_load(&rin[o]);
-        bufa[0][t] = (mode == MODE_STEP) ? ap[o] : T(0);
-    }
+        for (int t = 0; t < CH; ++t) load(t, bufr[0][t], bufa[0][t]);
 #pragma unroll
-    for (int cb = 0; cb < NCH; ++cb) {
-        const int b = cb & 1;
-        // keep the pipeline depth at one chunk: without this fence the
-        // scheduler hoists every chunk's loads and the half column's raw
-        // values all sit in registers at once (occupancy 1)
-        __builtin_amdgcn_sched_barrier(0);
-        if (cb + 1 < NCH) {
+        for (int cb = 0; cb < NCH; ++cb) {
+            const int b = cb & 1;
+            // keep the pipeline depth at one chunk: without this fence the
+            // scheduler hoists every chunk's loads and the half column's raw
+            // values all sit in registers at once (occupancy 1)
+            __builtin_amdgcn_sched_barrier(0);
+            if (cb + 1 < NCH) {
+#pragma unroll
+                for (int t = 0; t < CH; ++t) load((cb + 1) * CH + t, bufr[b ^ 1][t], bufa[b ^ 1][t]);
+            }
 #pragma unroll
             for (int t = 0; t < CH; ++t) {
-                const int q = (cb + 1) * CH + t;
-                int k = upper ? nz - 1 - q : q;
-                k = k < 0 ? 0 : (k > nz - 1 ? nz - 1 : k);
-                const long long o = (long long)colc + plane * k;
-                bufr[b ^ 1][t] = __builtin_nontemporal_load(&rin[o]);
-                bufa[b ^ 1][t] = (mode == MODE_STEP) ? ap[o] : T(0);
+                const int q = cb * CH + t;
+                const bool mine = q >= PAD || q >= pad;
+                const double v = (mode == MODE_STEP) ? fma(beta, (double)bufa[b][t], (double)bufr[b][t])
+                                 : (mode == MODE_GM) ? (double)bufr[b][t] / den
+                                                     : (double)bufr[b][t];
+                const T sv = (T)v;
+                const double rp_ = (double)sv;
+                if (mode == MODE_STEP || mode == MODE_GM) {
+                    if (mine) *rw = sv;
+                    rw += (q < PAD && q < walk) ? 0 : step;
+                }
+                // (selected, not multiplied: an empty row's Inf would leave NaN)
+                const double vn = mine ? v : 0.0, vs = mine ? rp_ : 0.0;
+                acc_new = fma(vn, vn, acc_new);
+                acc_st = fma(vs, vs, acc_st);
+                const CT w_in = face(q);
+                const CT wb = upper ? w_in : w_out;
+                const CT wa = upper ? w_out : w_in;
+                const CT diag = opsig_c * ((fma(s_lev[upper][q], h1, h0) + wb) + wa);
+                mk = diag + w_out * carry_g;
+                fk = (CT)sv + w_out * carry_d;
+                // binary32 column solve: the hardware reciprocal (about 1 ulp;
+                // the preconditioner only has to be a fixed operator); FP64:
+                // the correctly rounded quotient
+                CT inv;
+                if constexpr (sizeof(CT) == 4) inv = __builtin_amdgcn_rcpf(mk);
+                else inv = CT(1) / mk;
+                // (an empty row leaves 0: the next row's outer face is 0 too)
+                carry_g = mine ? -w_in * inv : CT(0);
+                carry_d = mine ? fk * inv : CT(0);
+                w_out = w_in;
+                if (q < LH) {
+                    s_stk[q < LH ? q : 0][0][threadIdx.x] = carry_g;
+                    s_stk[q < LH ? q : 0][1][threadIdx.x] = carry_d;
+                } else {
+                    ga[q - LH] = carry_g;
+                    de[q - LH] = carry_d;
+                    settle(ga[q - LH]);
+                    settle(de[q - LH]);
+                }
             }
         }
+        // meeting row (the lower lane's last): the lower lane gets (zeta_h,
+        // eps_h) from its upper partner
+        const CT zx = __shfl_xor(carry_g, 32);
+        const CT ex = __shfl_xor(carry_d, 32);
+        const CT xm = (fk + w_out * ex) / (mk + w_out * zx);
+        const CT xl = __shfl_xor(xm, 32);
+        // back-substitution: the lower lane from the meeting value at row
+        // H - 1 outward, the upper lane from its row H - 1 on
+        CT xv = upper ? carry_d - carry_g * xl : xm;
+        gptr_mut<T> ep = as_global_mut(eout) + (long long)col + plane * (upper ? h : h - 1);
+        asm volatile("" : "+v"(ep));
+        if (!(upper && nmine == 0)) *ep = (T)xv;
 #pragma unroll
-        for (int t = 0; t < CH; ++t) {
-            const int q = cb * CH + t;
-            const bool mine = q < nmine;
-            int k = upper ? nz - 1 - q : q;
-            k = k < 0 ? 0 : (k > nz - 1 ? nz - 1 : k);
-            const double v = (mode == MODE_STEP) ? fma(beta, (double)bufa[b][t], (double)bufr[b][t])
-                             : (mode == MODE_GM) ? (double)bufr[b][t] / den
-                                                 : (double)bufr[b][t];
-            const T sv = (T)v;
-            const double rp = (double)sv;
-            const CT rc = (CT)sv;
-            // When the columns fill the grid exactly (FULL), every lane owns
-            // every row it touches and stores r+ unguarded: behind a guard
-            // the compiler moves all rows' eliminations after all the
-            // stores, holding every row's values at once
-            if constexpr (FULL) {
-                if (mode == MODE_STEP || mode == MODE_GM) *rw = sv;
-                acc_new = fma(v, v, acc_new);
-                acc_st = fma(rp, rp, acc_st);
-            } else if (mine && valid) {
-                if (mode == MODE_STEP || mode == MODE_GM) *rw = sv;
-                acc_new = fma(v, v, acc_new);
-                acc_st = fma(rp, rp, acc_st);
-            }
-            rw += wstep;
-            // vertical face weights of row k: the face shared with the
-            // previous row of this lane was computed there (w_near); the far
-            // face (k + 1 for the lower lane, k for the upper one) is new
-            const int f = upper ? k : k + 1;
-            const CT gff = s_gf[f];
-            const CT w_far = (f > 0 && f < nz) ? gz * fma(hc, gff, CT(1)) : CT(0);
-            const CT wb = upper ? w_far : w_near;
-            const CT wa = upper ? w_near : w_far;
-            w_near = w_far;
-            const CT diag = opsig_c * ((fma(s_gc[k], h1, h0) + wb) + wa);
-            const CT near = upper ? -wa : -wb;
-            const CT far = upper ? -wb : -wa;
-            const CT mk = (q == 0) ? diag : diag - near * carry_g;
-            const CT fk = (q == 0) ? rc : rc - near * carry_d;
-            const bool meet = !upper && q == h - 1;
-            if (meet) {
-                mm = mk;
-                ff = fk;
-                uu = far;
-            }
-            // binary32 column solve: the hardware reciprocal (about 1 ulp;
-            // the preconditioner only has to be a fixed operator); FP64:
-            // the correctly rounded quotient
-            CT inv;
-            if constexpr (sizeof(CT) == 4) inv = __builtin_amdgcn_rcpf(mk);
-            else inv = CT(1) / mk;
-            const CT g_new = far * inv;
-            const CT d_new = fk * inv;
-            if (mine) {
-                carry_g = meet ? carry_g : g_new;
-                carry_d = meet ? carry_d : d_new;
-            }
-            if (q < LH) {
-                s_stk[q < LH ? q : 0][0][threadIdx.x] = g_new;
-                s_stk[q < LH ? q : 0][1][threadIdx.x] = d_new;
-            } else {
-                ga[q - LH] = g_new;
-                de[q - LH] = d_new;
-            }
-        }
-    }
-    // meeting row: the lower lane gets (zeta_h, eps_h) from its upper partner
-    const CT zx = __shfl_xor(carry_g, 32);
-    const CT ex = __shfl_xor(carry_d, 32);
-    const CT xm = (ff - uu * ex) / (mm - uu * zx);
-    const CT xl = __shfl_xor(xm, 32);
-    // back-substitution: lower lane from level h-2 down to 0 (after storing
-    // the meeting value at h-1), upper lane from level h up to nz-1
-    CT xv = upper ? xl : xm;
-    if (valid && !upper) eout[(long long)colc + plane * (h - 1)] = (T)xm;
-    const int nback = upper ? nup : h - 1;
-    // the store address walks one level per row from a fresh base: were it
-    // recomputed from the forward sweep's expressions, the compiler would
-    // keep all of the half column's 64-bit addresses live across the sweep
-    const long long estep = upper ? plane : -plane;
-    gptr_mut<T> ep = as_global_mut(eout) + (long long)colc + plane * (upper ? h : h - 2);
-    asm volatile("" : "+v"(ep));
-#pragma unroll
-    for (int q = H - 1; q >= 0; --q) {
-        if (q < nback) {
+        for (int q = H - 2; q >= 0; --q) {
             CT gq, dq;
             if (q < LH) {
                 gq = s_stk[q < LH ? q : 0][0][threadIdx.x];
@@ -792,8 +787,8 @@ __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in,
                 dq = de[q - LH];
             }
             xv = dq - gq * xv;
-            if (valid) *ep = (T)xv;
-            ep += estep;
+            ep -= step;
+            if (q >= PAD || q >= pad) *ep = (T)xv;
         }
     }
     if (mode == MODE_DEBUG || mode == MODE_GM) return;
@@ -805,32 +800,20 @@ __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in,
     }
 }
 
-template <typename T, int H, int mode>
-__global__ __launch_bounds__(COL_THREADS) void k_update_thomas(Table<T> tb, const T* dbg_in, T* dbg_out)
+// Two waves per SIMD (the longest columns need the hint to stay within 256
+// registers)
+template <typename T, int H, int mode, bool ANY = false>
+__global__ __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_update_thomas(
+    Table<T> tb, const T* dbg_in, T* dbg_out)
 {
-    update_thomas_body<T, H, mode, false>(tb, dbg_in, dbg_out, nullptr);
-}
-
-// The step pass on columns that fill the grid exactly, held to two waves
-// per SIMD (its unguarded stores keep the long columns within 256 registers)
-template <typename T, int H>
-__global__ __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_update_thomas_full(
-    Table<T> tb)
-{
-    update_thomas_body<T, H, MODE_STEP, true>(tb, nullptr, nullptr, nullptr);
+    update_thomas_body<T, H, mode, ANY>(tb, dbg_in, dbg_out, nullptr);
 }
 
 template <int H>
-__global__ __launch_bounds__(COL_THREADS) void k_update_thomas_gm(Table<double> tb, const GmInst* gm)
-{
-    update_thomas_body<double, H, MODE_GM, false>(tb, nullptr, nullptr, gm);
-}
-
-template <int H>
-__global__ __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_update_thomas_gm_full(
+__global__ __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_update_thomas_gm(
     Table<double> tb, const GmInst* gm)
 {
-    update_thomas_body<double, H, MODE_GM, true>(tb, nullptr, nullptr, gm);
+    update_thomas_body<double, H, MODE_GM, false>(tb, nullptr, nullptr, gm);
 }
 
 // The binary32 column pass with one lane per column (256 columns per
@@ -954,6 +937,8 @@ __global__ __launch_bounds__(COL_THREADS) void k_update_thomas1(Table<T> tb)
             }
             ga[q] = g_new;
             de[q] = d_new;
+            settle(ga[q]);
+            settle(de[q]);
         }
     }
     // back-substitution from the top level down
@@ -1709,6 +1694,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_debug_apply_A(Table<double> tb, 
     case 24: { constexpr int HV = 24; CALL; } break;      \
     case 28: { constexpr int HV = 28; CALL; } break;      \
     case 32: { constexpr int HV = 32; CALL; } break;      \
+    case 40: { constexpr int HV = 40; CALL; } break;      \
     default: { constexpr int HV = 48; CALL; } break;      \
     }
 
@@ -1719,7 +1705,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_debug_apply_A(Table<double> tb, 
 int thomas_depth(int nz)
 {
     const int h = (nz + 1) / 2;
-    const int depths[] = {4, 8, 16, 24, 28, 32, 48};
+    const int depths[] = {4, 8, 16, 24, 28, 32, 40, 48};
     for (int d : depths)
         if (h <= d) return d;
     return -1;
@@ -1797,10 +1783,18 @@ void Launch<T>::update_thomas(const Table<T>& tb, int total, int H, int mode, hi
             return;
         }
     }
-    if (mode == MODE_STEP && tb.full)
-        FTGCR_H_SWITCH(H, FTGCR_TIMED_LAUNCH(e0, e1, (k_update_thomas_full<T, HV>), dim3(total), dim3(COL_THREADS),
-                                             s, tb))
-    else if (mode == MODE_STEP)
+    if constexpr (sizeof(T) == 8) {
+        if (tb.mixed_depth) {
+            if (mode == MODE_STEP)
+                FTGCR_H_SWITCH(H, FTGCR_TIMED_LAUNCH(e0, e1, (k_update_thomas<T, HV, MODE_STEP, true>), dim3(total),
+                                                     dim3(COL_THREADS), s, tb, (const T*)nullptr, (T*)nullptr))
+            else
+                FTGCR_H_SWITCH(H, hipLaunchKernelGGL((k_update_thomas<T, HV, MODE_INIT, true>), dim3(total),
+                                                     dim3(COL_THREADS), 0, s, tb, (const T*)nullptr, (T*)nullptr))
+            return;
+        }
+    }
+    if (mode == MODE_STEP)
         FTGCR_H_SWITCH(H, FTGCR_TIMED_LAUNCH(e0, e1, (k_update_thomas<T, HV, MODE_STEP>), dim3(total),
                                              dim3(COL_THREADS), s, tb, (const T*)nullptr, (T*)nullptr))
     else
@@ -2570,11 +2564,7 @@ void GmLaunch::precond(const Table<double>& tb, const GmInst* gi, int nblk_col, 
                            (const double*)nullptr, (double*)nullptr, gi, COLS_PER_BLOCK);
         return;
     }
-    if (tb.full)
-        FTGCR_H_SWITCH(H, hipLaunchKernelGGL((k_update_thomas_gm_full<HV>), dim3(nblk_col), dim3(COL_THREADS), 0, s,
-                                             tb, gi))
-    else
-        FTGCR_H_SWITCH(H, hipLaunchKernelGGL((k_update_thomas_gm<HV>), dim3(nblk_col), dim3(COL_THREADS), 0, s, tb,
+    FTGCR_H_SWITCH(H, hipLaunchKernelGGL((k_update_thomas_gm<HV>), dim3(nblk_col), dim3(COL_THREADS), 0, s, tb,
                                              gi))
 }
 

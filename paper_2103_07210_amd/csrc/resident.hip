@@ -111,15 +111,6 @@ __device__ __forceinline__ void fence_rows()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// The value is formed here: its arithmetic is not moved to where it is used
-// (which would keep all operands instead of the result), and what follows from
-// it is not formed once before the step loop (and kept).
-template <typename V>
-__device__ __forceinline__ void settle(V& v)
-{
-    asm volatile("" : "+v"(v));
-}
-
 }  // namespace
 
 // A wavefront holds RES_COLS columns, lanes 0..31 their lower halves, lanes
@@ -869,6 +860,13 @@ const void* resident_kernel(int mesh, int H, int waves)
         FTGCR_RES(24)
         FTGCR_RES(28)
         FTGCR_RES(32)
+    case 40:
+        if constexpr (sizeof(T) == 4) {
+            if (waves <= 4)
+                return mesh == FTGCR_MESH_OCTAHEDRAL ? (const void*)k_resident<T, 40, FTGCR_MESH_OCTAHEDRAL, 4>
+                                                     : (const void*)k_resident<T, 40, FTGCR_MESH_LATLON, 4>;
+        }
+        return nullptr;
     case 48:
         if constexpr (sizeof(T) == 4) {
             if (waves <= 4)
