@@ -85,6 +85,8 @@ struct ftgcr_handle {
     // the resident kernel's shape (res_waves 0: this grid does not take it) and
     // exchange words (device)
     int res_waves = 0, nblk_res = 0, rtx = 0;
+    int cus = 0;              // of the device
+    bool no_resident = false; // a tuner is timing the streaming kernels
     unsigned long long* xw = nullptr;
 
     int nblk_col = 0, nblk_st = 0, nblk_dir = 0;
@@ -312,9 +314,8 @@ ftgcr_status setup_resident(ftgcr_handle* h)
     if (h->precond != FTGCR_PRECOND_COLUMN) return FTGCR_OK;
     const bool mixed = h->precision == FTGCR_MIXED;
     const Geo& g = h->geo;
-    int cus = 0;
-    HIP_TRY(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device));
-    const int w = resident_waves(g.mesh, g.nx, g.ny, h->H, mixed ? 4 : 8, cus, &h->rtx, &h->nblk_res);
+    HIP_TRY(h, hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device));
+    const int w = resident_waves(g.mesh, g.nx, g.ny, h->H, mixed ? 4 : 8, h->cus, &h->rtx, &h->nblk_res);
     if (w == 0 || !(mixed ? resident_fits<float>(g.mesh, h->H, w, h->nblk_res, h->kmax)
                           : resident_fits<double>(g.mesh, h->H, w, h->nblk_res, h->kmax)))
         return FTGCR_OK;
@@ -327,7 +328,7 @@ ftgcr_status setup_resident(ftgcr_handle* h)
 // A tiling asked for in the options means the streaming kernels.
 bool use_resident(const ftgcr_handle* h)
 {
-    return h->res_waves > 0 && h->opt.levels_per_block == 0 && h->opt.order_stencil == FTGCR_ORDER_AUTO &&
+    return h->res_waves > 0 && !h->no_resident && h->opt.levels_per_block == 0 && h->opt.order_stencil == FTGCR_ORDER_AUTO &&
            h->opt.order_dir == FTGCR_ORDER_AUTO;
 }
 
@@ -1341,6 +1342,184 @@ void batch_step(const Table<double>& tb, const BatchShape& sh, int H, int kc, bo
     L::finish_beta(tb, 0, s);
 }
 
+// How a batch runs in the resident kernel: its members by template depth, a
+// number of wavefronts per block for each depth.  A launch takes one block per
+// CU at most, so members of a depth go together as far as their blocks fit:
+// the fewest wavefronts per block with which all of them do (the quickest
+// step), else the most the depth allows (the most cells in flight: two
+// 256 x 128 x 32 members at 8 wavefronts take 41 us a step together, one at 4
+// takes 22).
+struct ResidentBatch {
+    struct Depth {
+        int H, waves;
+        std::vector<int> members;
+    };
+    std::vector<Depth> depths;
+    std::vector<int> rtx, nblk;   // per member
+};
+
+// Whether every member of the batch runs there (else the batch streams).
+bool plan_resident_batch(ftgcr_handle* const* hs, int n, int k, ResidentBatch& rb)
+{
+    rb.rtx.assign(n, 0);
+    rb.nblk.assign(n, 0);
+    std::map<int, std::vector<int>> by_depth;
+    for (int m = 0; m < n; ++m) {
+        if (!use_resident(hs[m])) return false;
+        by_depth[hs[m]->H].push_back(m);
+    }
+    const int cus = hs[0]->cus, mesh = hs[0]->geo.mesh;
+    const int most = std::min(cus, RES_BLOCKS);
+    for (const auto& d : by_depth) {
+        const int H = d.first;
+        int waves = 0;
+        for (int w = 1; w <= RES_WAVES; w *= 2) {
+            long long total = 0;
+            bool fits = true;
+            for (int m : d.second) {
+                const Geo& g = hs[m]->geo;
+                int tx = 0, nb = 0;
+                fits = fits && resident_shape(mesh, g.nx, g.ny, H, 8, cus, w, &tx, &nb);
+                total += nb;
+            }
+            if (!fits || !resident_fits<double>(mesh, H, w, most, k)) continue;
+            waves = w;
+            if (total <= most) break;
+        }
+        if (waves == 0) return false;
+        for (int m : d.second) {
+            const Geo& g = hs[m]->geo;
+            resident_shape(mesh, g.nx, g.ny, H, 8, cus, waves, &rb.rtx[m], &rb.nblk[m]);
+        }
+        rb.depths.push_back({H, waves, d.second});
+    }
+    return true;
+}
+
+// The steps of a batch planned by plan_resident_batch, from every member's
+// start to its outcome.  Members with fault events ahead run first, each to
+// the step before its next one; once none is left, all run to their end.
+// inst, blk0, status: device tables with room for n members; single(m) the
+// member's own launch table, apply(m, event) injects an event.
+template <class Single, class Apply>
+ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const ResidentBatch& rb,
+                                const std::vector<Inst<double>>& ins, const std::vector<std::vector<DevEvent>>& evs,
+                                const Table<double>& tb_all, long long* status, Inst<double>* inst, int* blk0,
+                                Single&& single, Apply&& apply)
+{
+    using L = Launch<double>;
+    ftgcr_handle* h0 = hs[0];
+    hipStream_t s = h0->stream;
+    const int most = std::min(h0->cus, RES_BLOCKS);
+    std::vector<size_t> evp(n, 0);
+    std::vector<char> resident_norms(n, 0);   // the member's state holds the resident kernel's norms
+    std::vector<long long> host(2 * n), before(n, -1);
+    std::vector<char> launched(n, 0);
+    while (true) {
+        L::gather_status(tb_all, status, s);
+        HIP_TRY(h0, hipMemcpyAsync(host.data(), status, 2 * n * sizeof(long long), hipMemcpyDeviceToHost, s));
+        HIP_TRY(h0, hipStreamSynchronize(s));
+        bool any = false, ahead = false;
+        for (int m = 0; m < n; ++m) {
+            if (host[2 * m] != RUNNING) continue;
+            any = true;
+            if (launched[m] && host[2 * m + 1] <= before[m])
+                return fail(h0, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
+            while (evp[m] < evs[m].size() && evs[m][evp[m]].step <= host[2 * m + 1]) ++evp[m];
+            ahead = ahead || evp[m] < evs[m].size();
+        }
+        if (!any) return FTGCR_OK;
+        std::fill(launched.begin(), launched.end(), 0);
+        std::vector<Inst<double>> act;
+        std::vector<int> pre;
+        struct Go {
+            const ResidentBatch::Depth* d;
+            int first, at, count, blocks;
+        };
+        std::vector<Go> gos;
+        bool streamed = false;
+        for (const auto& d : rb.depths) {
+            std::vector<std::vector<int>> bins;   // members of one launch, first fit by falling block counts
+            std::vector<int> room;
+            std::vector<Inst<double>> go_in;
+            for (int m : d.members) {
+                if (host[2 * m] != RUNNING || (ahead && evp[m] >= evs[m].size())) continue;
+                const long long next = host[2 * m + 1] + 1;
+                bool now = evp[m] < evs[m].size() && evs[m][evp[m]].step == next, stream = false;
+                if (now) {
+                    size_t end = evp[m];
+                    for (; end < evs[m].size() && evs[m][end].step == next; ++end)
+                        stream = stream || evs[m][end].vec == FTGCR_V_E ||
+                                 (evs[m][end].vec == FTGCR_V_R && !resident_norms[m]);
+                    if (stream) {   // this step in the streaming kernels
+                        const Table<double> t1 = single(m);
+                        if (resident_norms[m]) L::norms(t1, ins[m].nblk_col, hs[m]->H, s);
+                        resident_norms[m] = 0;
+                        std::vector<std::pair<int, const DevEvent*>> mid;
+                        for (; evp[m] < end; ++evp[m]) {
+                            if (evs[m][evp[m]].vec == FTGCR_V_E) mid.push_back({m, &evs[m][evp[m]]});
+                            else apply(m, evs[m][evp[m]]);
+                        }
+                        BatchShape one;
+                        one.n = 1;
+                        one.cols = ins[m].nblk_col;
+                        one.sts = ins[m].nblk_st;
+                        one.dirs = ins[m].nblk_dir;
+                        batch_step(t1, one, hs[m]->H, ins[m].kc, nt_ap_hint(k, hs[m]->geo.n, 8), s, mid, apply);
+                        streamed = true;
+                        continue;
+                    }
+                    for (; evp[m] < end; ++evp[m]) apply(m, evs[m][evp[m]]);
+                }
+                Inst<double> in = ins[m];
+                in.rtx = rb.rtx[m];
+                in.nblk_res = rb.nblk[m];
+                in.res_new_norms = resident_norms[m] ? 0 : 1;
+                in.res_stop = next - 1 + RES_STEPS;
+                if (evp[m] < evs[m].size()) in.res_stop = std::min<long long>(in.res_stop, evs[m][evp[m]].step - 1);
+                resident_norms[m] = 1;
+                before[m] = next - 1;
+                launched[m] = 1;
+                go_in.push_back(in);
+            }
+            std::stable_sort(go_in.begin(), go_in.end(),
+                             [](const Inst<double>& a, const Inst<double>& b) { return a.nblk_res > b.nblk_res; });
+            for (int q = 0; q < (int)go_in.size(); ++q) {
+                size_t b = 0;
+                while (b < bins.size() && room[b] < go_in[q].nblk_res) ++b;
+                if (b == bins.size()) {
+                    bins.emplace_back();
+                    room.push_back(most);
+                }
+                bins[b].push_back(q);
+                room[b] -= go_in[q].nblk_res;
+            }
+            for (const auto& bin : bins) {
+                Go go{&d, (int)pre.size(), (int)act.size(), (int)bin.size(), 0};
+                pre.push_back(0);
+                for (int q : bin) {
+                    act.push_back(go_in[q]);
+                    go.blocks += go_in[q].nblk_res;
+                    pre.push_back(go.blocks);
+                }
+                gos.push_back(go);
+            }
+        }
+        if (act.empty() && !streamed) return fail(h0, FTGCR_E_HIP, "batched step loop did not terminate");
+        if (act.empty()) continue;
+        HIP_TRY(h0, hipMemcpyAsync(inst, act.data(), act.size() * sizeof(Inst<double>), hipMemcpyHostToDevice, s));
+        HIP_TRY(h0, hipMemcpyAsync(blk0, pre.data(), pre.size() * sizeof(int), hipMemcpyHostToDevice, s));
+        for (const Go& go : gos) {
+            Table<double> t{};
+            t.inst = inst + go.at;
+            t.n = go.count;
+            HIP_TRY(h0, resident_run<double>(t, blk0 + go.first, go.blocks, h0->geo.mesh, go.d->H, go.d->waves,
+                                             ResidentArgs{-1, k + 1, 0, 0, 0}, s));
+        }
+        HIP_TRY(h0, hipStreamSynchronize(s));   // act and pre are read until here
+    }
+}
+
 // Members step together: each launch of a step kernel covers the blocks of
 // every member of the launch table (block -> member by a prefix search),
 // and the one-block reductions run one block per member.  All members share
@@ -1403,7 +1582,7 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
     rc = upload_batch(h0, ins, members, H, B.inst, B.blk0, sh, tb);
     if (rc != FTGCR_OK) return rc;
     auto single = [&](int m) {
-        return Table<double>{B.all + m, hs[m]->blk0, hs[m]->blk0 + 2, hs[m]->blk0 + 4, 1, FTGCR_MESH_LATLON,
+        return Table<double>{B.all + m, hs[m]->blk0, hs[m]->blk0 + 2, hs[m]->blk0 + 4, 1, h0->geo.mesh,
                              h0->precond};
     };
 
@@ -1459,6 +1638,12 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
         HIP_TRY(h0, hipGraphLaunch(B.graph, s));
         return FTGCR_OK;
     };
+    ResidentBatch rb;
+    if (plan_resident_batch(hs, n, k, rb)) {
+        rc = run_resident_batch(hs, n, k, rb, ins, evs, tb_all, B.status, B.inst, B.blk0, single, apply);
+        if (rc != FTGCR_OK) return rc;
+        members.clear();
+    }
     while (!members.empty()) {
         // fault events of the next step, member by member: x, r, p, L(p)
         // events now, e events between the step's decision and its stencil
@@ -1923,12 +2108,16 @@ ftgcr_status ftgcr_autotune_batch(ftgcr_handle* const* hs, int32_t n, const doub
     std::vector<ftgcr_options> saved(n);
     for (int m = 0; m < n; ++m) saved[m] = hs[m]->opt;
     auto restore = [&]() {
-        for (int m = 0; m < n; ++m) (void)ftgcr_set_options(hs[m], &saved[m]);
+        for (int m = 0; m < n; ++m) {
+            hs[m]->no_resident = false;
+            (void)ftgcr_set_options(hs[m], &saved[m]);
+        }
     };
     for (int m = 0; m < n; ++m) {
         ftgcr_options o = saved[m];
         o.max_steps = steps;
         o.profile_kernels = 0;
+        hs[m]->no_resident = true;   // the tiling of the streaming kernels is what is timed
         ftgcr_status rc = ftgcr_set_options(hs[m], &o);
         if (rc != FTGCR_OK) {
             restore();

@@ -185,6 +185,9 @@ struct Inst {
     // the resident kernel's exchange words, blocks and tiles in x
     unsigned long long* xw;
     int nblk_res, rtx;
+    // of a batch's launch (ResidentArgs::s_stop < 0): this member's
+    int res_new_norms;
+    long long res_stop;
 };
 
 // FT-GMRES(k) control state of one solve (device memory; written by single
@@ -265,12 +268,14 @@ constexpr size_t RES_WORDS = 2 * (size_t)RES_COPIES * NV_MAX * RES_BLOCKS * 2;
 // half columns of depth H on at most `cus` blocks (0: it does not), and its
 // tile counts.
 int resident_waves(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int* rtx, int* nblk);
+// The same for a given number of wavefronts per block (false: it does not).
+bool resident_shape(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int waves, int* rtx, int* nblk);
 // Whether the device can hold the kernel's blocks all at once.
 template <typename T> bool resident_fits(int mesh, int H, int waves, int nblk, int k);
 // What a launch runs: steps until every instance has left RUNNING or executed
 // s_stop of them.
 struct ResidentArgs {
-    long long s_stop;
+    long long s_stop;  // < 0: each instance's own (Inst::res_stop, res_new_norms)
     int nvmax;         // k + 1: the most sums in a round
     int new_norms;     // 1: form the state's norms of r anew first
     int time_mask, time_stride;   // options.profile_kernels

@@ -695,17 +695,14 @@ __device__ __forceinline__ void update_thomas_body(Table<T> tb, const T* dbg_in,
         const long long first = (long long)col + (upper && nmine > 0 ? plane * (nz - 1) : 0);
         const int walk = nmine > 0 ? pad : H;   // rows before this one do not move
         gptr<T> rp = as_global(rin) + first;
-        gptr<T> app = as_global(ap) + first;
+        // L(p) relative to r: one walking pointer for both
+        const long long to_ap = ((long long)ap - (long long)rin) / (long long)sizeof(T);
         gptr_mut<T> rw = as_global_mut((mode == MODE_STEP || mode == MODE_GM) ? rout : eout) + first;
-        asm volatile("" : "+v"(rp), "+v"(app), "+v"(rw));
+        asm volatile("" : "+v"(rp), "+v"(rw));
         auto load = [&](int q, T& rv, T& av) {
             rv = __builtin_nontemporal_load(rp);
-            av = (mode == MODE_STEP) ? *app : T(0);
-            const long long d = (q < PAD && q < walk) ? 0 : step;
-            if (q + 1 < H) {
-                rp += d;
-                app += d;
-            }
+            av = (mode == MODE_STEP) ? rp[to_ap] : T(0);
+            if (q + 1 < H) rp += (q < PAD && q < walk) ? 0 : step;
         };
 #pragma unroll
         for (int t = 0; t < CH; ++t) load(t, bufr[0][t], bufa[0][t]);

@@ -410,7 +410,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
 
     // the detector compares norms of r summed in one order: these two (of r and
     // of the backup's) come from the streaming kernels
-    if (arg.new_norms && s_st.status == RUNNING) {
+    if ((arg.s_stop < 0 ? in.res_new_norms : arg.new_norms) && s_st.status == RUNNING) {
         const T* rp = uniform(s_R[s_st.r_bak]);
         double a0 = 0.0, a1 = 0.0;
 #pragma unroll
@@ -446,7 +446,8 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         tick = now;
     };
 
-    while (s_st.status == RUNNING && s_st.s < arg.s_stop) {
+    const long long s_stop = arg.s_stop < 0 ? in.res_stop : arg.s_stop;
+    while (s_st.status == RUNNING && s_st.s < s_stop) {
         const long long step = s_st.s + 1;
         timed(-1, step);
         const int nu = __builtin_amdgcn_readfirstlane(s_st.nu);
@@ -822,20 +823,25 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
 // Registers bound the depth: a half column of H levels holds five vectors of
 // H values per lane (r, L(p), the pivots, e, L(e)), 512 registers at one
 // wavefront per SIMD (four to a block), 256 at two.
+bool resident_shape(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int waves, int* rtx, int* nblk)
+{
+    const int hmax = waves <= 4 ? (elem_bytes == 4 ? 48 : 32) : (elem_bytes == 4 ? 32 : 16);
+    const int most = cus < RES_BLOCKS ? cus : RES_BLOCKS;
+    if (H > hmax) return false;
+    const bool oct = mesh == FTGCR_MESH_OCTAHEDRAL;
+    const long long wide = oct ? (long long)RES_COLS * waves : RES_COLS;
+    const long long tx = (nx + wide - 1) / wide;
+    const long long blocks = tx * (oct ? 1 : (ny + waves - 1) / waves);
+    if (blocks > most) return false;
+    *rtx = (int)tx;
+    *nblk = (int)blocks;
+    return true;
+}
+
 int resident_waves(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int* rtx, int* nblk)
 {
-    const int hmax4 = elem_bytes == 4 ? 48 : 32, hmax8 = elem_bytes == 4 ? 32 : 16;
-    const int most = cus < RES_BLOCKS ? cus : RES_BLOCKS;
-    for (int w = 1; w <= RES_WAVES; w *= 2) {
-        if (H > (w <= 4 ? hmax4 : hmax8)) return 0;
-        const long long tx = mesh == FTGCR_MESH_OCTAHEDRAL ? ((long long)nx + RES_COLS * w - 1) / (RES_COLS * w)
-                                                           : ((long long)nx + RES_COLS - 1) / RES_COLS;
-        const long long blocks = tx * (mesh == FTGCR_MESH_OCTAHEDRAL ? 1 : (ny + w - 1) / w);
-        if (blocks > most) continue;
-        *rtx = (int)tx;
-        *nblk = (int)blocks;
-        return w;
-    }
+    for (int w = 1; w <= RES_WAVES; w *= 2)
+        if (resident_shape(mesh, nx, ny, H, elem_bytes, cus, w, rtx, nblk)) return w;
     return 0;
 }
 
