@@ -1135,6 +1135,7 @@ ftgcr_status gm_solve_impl(ftgcr_handle* h, const double* rhs, double* x, double
     const Table<double> tb{h->inst_dbg, h->blk0, h->blk0 + 2, h->blk0 + 4, 1, h->geo.mesh, h->precond};
     const int nblk_col = (h->geo.ncols + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
     const int nst = h->nblk_st, kc = h->kc;
+    const bool nt = nt_ap_hint(k, h->geo.n, (int)sizeof(double));
     GmState* hs = h->gm_host;
     auto read_head = [&]() -> ftgcr_status {
         HIP_TRY(h, hipGetLastError());
@@ -1159,15 +1160,15 @@ ftgcr_status gm_solve_impl(ftgcr_handle* h, const double* rhs, double* x, double
             ap = ap || ev->vec == FTGCR_V_AP;
         }
         if (ap) {
-            G::stencil(d, nst, kc, 0, h->geo.mesh, s);
+            G::stencil(d, nst, kc, 0, h->geo.mesh, nt, s);
             for (const DevEvent* ev : at)
                 if (ev->vec == FTGCR_V_AP) inject(*ev, t);
             G::dots(d, nst, kc, s);
         } else {
-            G::stencil(d, nst, kc, 1, h->geo.mesh, s);
+            G::stencil(d, nst, kc, 1, h->geo.mesh, nt, s);
         }
         G::finish_h(d, s);
-        G::orth(d, nst, kc, s);
+        G::orth(d, nst, kc, nt, s);
         G::finish_step(d, s);
     };
     HIP_TRY(h, hipEventRecord(h->ev_start, s));
@@ -1202,7 +1203,7 @@ ftgcr_status gm_solve_impl(ftgcr_handle* h, const double* rhs, double* x, double
         } else {
             for (int j = 0; j < k; ++j) step(none, 0);
         }
-        G::xupd(d, nst, kc, s);
+        G::xupd(d, nst, kc, nt, s);
         G::finish_x(d, s);
     }
     G::finalize(d, nst, kc, s);

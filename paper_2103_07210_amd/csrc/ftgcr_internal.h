@@ -328,12 +328,13 @@ struct GmLaunch {
     static void restart(const GmInst* gi, hipStream_t s);
     static void precond(const Table<double>& tb, const GmInst* gi, int nblk_col, int H, hipStream_t s);
     // dots = 0: store A z_j only (the dots follow a fault event on it)
-    static void stencil(const GmInst* gi, int nblk_st, int kc, int dots, int mesh, hipStream_t s);
+    // nt: the basis does not fit the cache (nt_ap_hint)
+    static void stencil(const GmInst* gi, int nblk_st, int kc, int dots, int mesh, bool nt, hipStream_t s);
     static void dots(const GmInst* gi, int nblk_st, int kc, hipStream_t s);
     static void finish_h(const GmInst* gi, hipStream_t s);
-    static void orth(const GmInst* gi, int nblk_st, int kc, hipStream_t s);
+    static void orth(const GmInst* gi, int nblk_st, int kc, bool nt, hipStream_t s);
     static void finish_step(const GmInst* gi, hipStream_t s);
-    static void xupd(const GmInst* gi, int nblk_st, int kc, hipStream_t s);
+    static void xupd(const GmInst* gi, int nblk_st, int kc, bool nt, hipStream_t s);
     static void finish_x(const GmInst* gi, hipStream_t s);
     static void finalize(const GmInst* gi, int nblk_st, int kc, hipStream_t s);
     static void event_prep(const GmInst* gi, int vec, long long step, hipStream_t s);

@@ -2152,7 +2152,16 @@ __global__ __launch_bounds__(RED_THREADS) void k_gm_restart(const GmInst* gi)
 // v_{i+1} are issued before v_i's values are used (two buffers alternating
 // with the parity of i), so the terms cost one memory round trip together
 // rather than one each.
-template <int KC>
+// NT: the Arnoldi vectors are loaded with the non-temporal hint (nt_ap_hint:
+// the cycle's vectors do not fit the Infinity Cache, which is then left to
+// z_j, w and v_{j+1}, read again within the step).
+template <bool NT>
+__device__ __forceinline__ double gm_load(const double* p)
+{
+    return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
+template <int KC, bool NT>
 __device__ __forceinline__ void gm_dots(const GmInst& in, const StPos& ps, const double (&w)[KC], int j)
 {
     __shared__ double sh[KMAX + 1][4];
@@ -2164,7 +2173,7 @@ __device__ __forceinline__ void gm_dots(const GmInst& in, const StPos& ps, const
 #pragma unroll
     for (int kk = 0; kk < KC; ++kk) {
         const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
-        buf[0][kk] = in.U[0][c0 + plane * kq];
+        buf[0][kk] = gm_load<NT>(&in.U[0][c0 + plane * kq]);
     }
 #pragma unroll
     for (int i = 0; i < KMAX; ++i) {
@@ -2174,7 +2183,7 @@ __device__ __forceinline__ void gm_dots(const GmInst& in, const StPos& ps, const
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk) {
                     const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
-                    buf[(i + 1) & 1][kk] = vn[c0 + plane * kq];
+                    buf[(i + 1) & 1][kk] = gm_load<NT>(&vn[c0 + plane * kq]);
                 }
             }
             double acc = 0.0;
@@ -2195,7 +2204,7 @@ __device__ __forceinline__ void gm_dots(const GmInst& in, const StPos& ps, const
 }
 
 // w = A z_j into W; with DOTS also the partials of <w, v_i>.
-template <int KC, int DOTS, int MESH>
+template <int KC, int DOTS, int MESH, bool NT>
 __global__ __launch_bounds__(ST_THREADS) void k_gm_stencil(const GmInst* gi)
 {
     const GmInst& in = *gi;
@@ -2214,7 +2223,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_gm_stencil(const GmInst* gi)
         if (ok) in.W[c0 + plane * (ps.k0 + kk)] = w[kk];
         else w[kk] = 0.0;
     }
-    if (DOTS) gm_dots<KC>(in, ps, w, j);
+    if (DOTS) gm_dots<KC, NT>(in, ps, w, j);
 }
 
 // The partials of <w, v_i> from the stored w (after a fault event on it).
@@ -2236,7 +2245,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_gm_dots(const GmInst* gi)
         const double v = in.W[c0 + plane * kq];
         w[kk] = ok ? v : 0.0;
     }
-    gm_dots<KC>(in, ps, w, st->j);
+    gm_dots<KC, false>(in, ps, w, st->j);
 }
 
 __global__ __launch_bounds__(RED_THREADS) void k_gm_finish_h(const GmInst* gi)
@@ -2253,7 +2262,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_gm_finish_h(const GmInst* gi)
 // Each cell takes the same operations in the same order as a loop over i
 // per cell; the loop over i runs outside (unrolled to KMAX, uniform guard)
 // with v_{i+1}'s loads issued before v_i is used.
-template <int KC>
+template <int KC, bool NT>
 __global__ __launch_bounds__(ST_THREADS) void k_gm_orth(const GmInst* gi)
 {
     __shared__ double sh[4];
@@ -2275,7 +2284,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_gm_orth(const GmInst* gi)
         const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
         const long long c = c0 + plane * kq;
         w[kk] = in.W[c];
-        buf[0][kk] = in.U[0][c];
+        buf[0][kk] = gm_load<NT>(&in.U[0][c]);
     }
 #pragma unroll
     for (int i = 0; i < KMAX; ++i) {
@@ -2285,7 +2294,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_gm_orth(const GmInst* gi)
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk) {
                     const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
-                    buf[(i + 1) & 1][kk] = vn[c0 + plane * kq];
+                    buf[(i + 1) & 1][kk] = gm_load<NT>(&vn[c0 + plane * kq]);
                 }
             }
             const double h = s_h[i];
@@ -2382,7 +2391,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_gm_finish_step(const GmInst* gi
 // The cycle's correction: y from the rotated triangular system over the
 // steps done, then x + sum_i y_i z_i (ascending i) into a buffer that is not
 // the backup.
-template <int KC>
+template <int KC, bool NT>
 __global__ __launch_bounds__(ST_THREADS) void k_gm_xupd(const GmInst* gi)
 {
     __shared__ double y[KMAX];
@@ -2417,7 +2426,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_gm_xupd(const GmInst* gi)
         const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
         const long long c = c0 + plane * kq;
         xv[kk] = xsrc[c];
-        buf[0][kk] = jd > 0 ? in.Z[0][c] : 0.0;
+        buf[0][kk] = jd > 0 ? gm_load<NT>(&in.Z[0][c]) : 0.0;
     }
 #pragma unroll
     for (int i = 0; i < KMAX; ++i) {
@@ -2427,7 +2436,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_gm_xupd(const GmInst* gi)
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk) {
                     const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
-                    buf[(i + 1) & 1][kk] = zn[c0 + plane * kq];
+                    buf[(i + 1) & 1][kk] = gm_load<NT>(&zn[c0 + plane * kq]);
                 }
             }
             const double yi = y[i];
@@ -2565,18 +2574,20 @@ void GmLaunch::precond(const Table<double>& tb, const GmInst* gi, int nblk_col, 
                                              gi))
 }
 
-void GmLaunch::stencil(const GmInst* gi, int nblk, int kc, int dots, int mesh, hipStream_t s)
+void GmLaunch::stencil(const GmInst* gi, int nblk, int kc, int dots, int mesh, bool nt, hipStream_t s)
 {
-#define FTGCR_GM_STENCIL(MV)                                                                                  \
-    if (dots)                                                                                                 \
-        FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_stencil<KCV, 1, MV>), dim3(nblk), dim3(ST_THREADS), 0, s, gi)) \
-    else                                                                                                      \
-        FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_stencil<KCV, 0, MV>), dim3(nblk), dim3(ST_THREADS), 0, s, gi))
+#define FTGCR_GM_STENCIL(MV, DV, NTV) \
+    FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_stencil<KCV, DV, MV, NTV>), dim3(nblk), dim3(ST_THREADS), 0, s, gi))
+#define FTGCR_GM_STENCIL_MESH(MV)                     \
+    if (!dots) FTGCR_GM_STENCIL(MV, 0, false)         \
+    else if (nt) FTGCR_GM_STENCIL(MV, 1, true)        \
+    else FTGCR_GM_STENCIL(MV, 1, false)
     if (mesh == FTGCR_MESH_OCTAHEDRAL) {
-        FTGCR_GM_STENCIL(FTGCR_MESH_OCTAHEDRAL)
+        FTGCR_GM_STENCIL_MESH(FTGCR_MESH_OCTAHEDRAL)
     } else {
-        FTGCR_GM_STENCIL(FTGCR_MESH_LATLON)
+        FTGCR_GM_STENCIL_MESH(FTGCR_MESH_LATLON)
     }
+#undef FTGCR_GM_STENCIL_MESH
 #undef FTGCR_GM_STENCIL
 }
 
@@ -2590,9 +2601,12 @@ void GmLaunch::finish_h(const GmInst* gi, hipStream_t s)
     hipLaunchKernelGGL(k_gm_finish_h, dim3(1), dim3(RED_THREADS), 0, s, gi);
 }
 
-void GmLaunch::orth(const GmInst* gi, int nblk, int kc, hipStream_t s)
+void GmLaunch::orth(const GmInst* gi, int nblk, int kc, bool nt, hipStream_t s)
 {
-    FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_orth<KCV>), dim3(nblk), dim3(ST_THREADS), 0, s, gi));
+    if (nt)
+        FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_orth<KCV, true>), dim3(nblk), dim3(ST_THREADS), 0, s, gi))
+    else
+        FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_orth<KCV, false>), dim3(nblk), dim3(ST_THREADS), 0, s, gi))
 }
 
 void GmLaunch::finish_step(const GmInst* gi, hipStream_t s)
@@ -2600,9 +2614,12 @@ void GmLaunch::finish_step(const GmInst* gi, hipStream_t s)
     hipLaunchKernelGGL(k_gm_finish_step, dim3(1), dim3(RED_THREADS), 0, s, gi);
 }
 
-void GmLaunch::xupd(const GmInst* gi, int nblk, int kc, hipStream_t s)
+void GmLaunch::xupd(const GmInst* gi, int nblk, int kc, bool nt, hipStream_t s)
 {
-    FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_xupd<KCV>), dim3(nblk), dim3(ST_THREADS), 0, s, gi));
+    if (nt)
+        FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_xupd<KCV, true>), dim3(nblk), dim3(ST_THREADS), 0, s, gi))
+    else
+        FTGCR_KC_SWITCH(kc, hipLaunchKernelGGL((k_gm_xupd<KCV, false>), dim3(nblk), dim3(ST_THREADS), 0, s, gi))
 }
 
 void GmLaunch::finish_x(const GmInst* gi, hipStream_t s)
