@@ -1223,12 +1223,13 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_step(Table<T> tb)
     // (the partials of a solve that is no longer running are read and
     // ignored)
     const long long word = state_word_load(gst);
+    const int status = gst->status;   // not the staged one: thread 0 changes that one below, without a barrier
     double v[2];
     sum_partials<2, 8>(in, in.nblk_col, 0, 2, v);
     state_word_stage(&s_st, word);
     __syncthreads();
     SolveState* st = &s_st;
-    if (st->status != RUNNING) return;
+    if (status != RUNNING) return;
     if (threadIdx.x == 0) decide_step(st, gst->log, v[0], v[1], in.hist, in.hist_cap);
     __syncthreads();
     if (st->status == RUNNING && st->active) finish_alpha_body(in, st);
@@ -1422,13 +1423,13 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_beta(Table<T> tb, int in
     const Inst<T>& in = tb.inst[blockIdx.x];
     SolveState* gst = in.st;
     const long long word = state_word_load(gst);
+    const int status = gst->status, active = gst->active;   // not the staged ones: see k_finish_step
     double v[2];
     sum_partials<2, 8>(in, in.nblk_dir, 0, 2, v);
     state_word_stage(&s_st, word);
     __syncthreads();
     SolveState* st = &s_st;
-    if (st->status != RUNNING) return;
-    if (!init && !st->active) return;
+    if (status != RUNNING || (!init && !active)) return;
     if (threadIdx.x == 0) decide_beta(st, v[0], v[1], init);
     __syncthreads();
     state_word_store(gst, st);
