@@ -2,7 +2,8 @@
 //
 // The engine builds the FP64 coefficient tables once per handle, lays the
 // working vectors out in the caller's workspace, and drives a solve as a
-// sequence of step launches on the handle's stream.  All decisions of
+// sequence of step launches on the handle's stream, or of launches of the
+// resident kernel with many steps each.  All decisions of
 // Algorithm 1 (exit, fault test, backup, rollback, cycle restart) are taken
 // on the device; the host only enqueues steps, inserts the harness's fault
 // events before the step they belong to, and reads one status word every
@@ -194,10 +195,10 @@ int auto_levels_per_block(int tx, int ty, int nz)
     return 1;
 }
 
-// The direction pass holds two values per direction term and level (p^l and
-// L(p^l), two pipeline stages), so it takes at most 4 levels per block: at 8
-// its FP64 form needs more than 128 registers and drops to two waves per SIMD
-// (measured 125 vs 118 us on 512x256x64, while the dots pass is fastest at 8).
+// The direction pass takes at most 4 levels per block: at 8 its FP64 form needs
+// 163 registers with the basis sums of a cycle's end and drops to three waves
+// per SIMD (512x256x64: FP64 83.7 vs 82.0 us, binary32 50.6 vs 48.0; O160x51
+// 58.2 vs 54.4), while the dots pass is fastest at 8 on the lat-lon mesh.
 void dir_tiling(int kc, int nz, int tx, int ty, int& kc_dir, int& tz_dir, int& nblk_dir)
 {
     kc_dir = kc < 4 ? kc : 4;

@@ -1,7 +1,8 @@
 // FT-GCR device kernels for gfx950 (MI355X).
 //
 // One inner step of Algorithm 1 (FT-GCR(k), arXiv 2103.07210) runs as three
-// streaming passes over HBM and two one-block reductions:
+// streaming passes over HBM and two one-block reductions (where the columns
+// fit the registers of the chip, the resident kernel takes their place):
 //
 //   update_thomas   r+ = r + beta L(p^nu), <r+, r+> partials, e = P^{-1} r+
 //   stencil_dots    L(e) and the partials of <L(e), L(p^l)>, l = 0..nu
@@ -10,9 +11,10 @@
 //     finish_step   exit test, monotone-norm fault test, backup or rollback
 //                   (Algorithm 1, red part), then
 //                   alpha_l = -<L(e), L(p^l)> / <L(p^l), L(p^l)>
-//   dir_update      p^{nu+1}, L(p^{nu+1}) (L(e) recomputed), the next beta's
-//                   inner products, and at the end of a cycle the deferred
-//                   iterate update phi += sum_l beta_l p^l
+//   dir_update      L(p^{nu+1}) (L(e) recomputed), the next beta's inner
+//                   products, and at the end of a cycle p^k and the deferred
+//                   iterate update phi += sum_l beta_l p^l, both summed over
+//                   the cycle's basis p^0, e^1 .. e^k
 //     finish_beta   beta, pass and cycle bookkeeping
 //
 // A step with faults to inject into e takes the decision in a launch of its
@@ -247,8 +249,9 @@ __device__ __forceinline__ void stencil_chunk(const Geo& g, const TI* __restrict
 // Depth of the direction-term load pipeline of the direction pass: the
 // loads of term l + TERM_PIPE - 1 are issued before term l is used.
 // binary32 loads carry half the bytes and the binary32 kernel has registers
-// to spare, so it keeps one more term in flight (64.1 vs 65.2 us on
-// 512 x 256 x 64; three stages in FP64 would cost occupancy).
+// to spare, so it keeps one more term in flight.  One stage more in either
+// form is within the noise (FP64 81.5 vs 82.0 us, binary32 47.8 vs 48.0 on
+// 512 x 256 x 64; O160 x 51 53.6 vs 54.4).
 template <typename T>
 constexpr int TERM_PIPE = sizeof(T) == 4 ? 3 : 2;
 
@@ -554,6 +557,11 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_residual(Table<T> tb, in
 // values in registers; settle() keeps a row's results formed beside its
 // loads.  The empty rows (levels a half is short of H) read the outermost
 // level's address, take no part in the sums and store nothing.
+//
+// Bound by memory where the solve exceeds the cache: r and L(p) read, r+ and
+// e written, 268 MB in 45 us at 512 x 256 x 64 (6 TB/s).  Columns that do not
+// fill their template take no longer per byte: O160 x 51 41.8 -> 33.3 us,
+// 700 x 333 x 47 83.6 -> 74.5 us against a guard on every row.
 
 // Most empty rows of a half column in the template of depth H (the next
 // smaller depth holds anything shorter).
@@ -819,7 +827,8 @@ __global__ __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(2))
 // its 4096 waves on 512 x 256 columns take 1.33 rounds of the chip at three
 // per SIMD; with one lane per column there are half as many waves, which fit
 // in one round at two per SIMD, and every load is a full 256-byte wave
-// segment.  Same update, norms, faces, diagonal and elimination as above
+// segment.  settle() beside each row's loads holds it at 155 registers (246
+// without: 27.4 -> 24.9 us on 512 x 256 x 64).  Same update, norms, faces, diagonal and elimination as above
 // (the lower lane's order, extended to the whole column), so P is the same
 // fixed operator up to rounding.
 template <typename T, int NZ, int mode>
@@ -1142,7 +1151,12 @@ __global__ __launch_bounds__(ST_THREADS) void k_stencil_dots(Table<T> tb, int sp
     // comes after term l + 1's loads are issued)
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     // PD - 1 terms in flight ahead of the one in use (a deeper pipeline
-    // costs this pass occupancy without a gain, measured in both forms)
+    // costs this pass occupancy without a gain, measured in both forms).  On
+    // the octahedral mesh the pass is a chain of round trips (state, slot
+    // tables, gathers, terms) at two waves per SIMD: O160 x 51 in FP64 68 us
+    // for 236 MB.  More waves by fewer registers spill (81 us at three, 130 at
+    // four), 4 levels a block take 66, the tables held over a loop of level
+    // chunks 74 to 84.
     constexpr int PD = 2;
     T buf[PD][KC];
 #pragma unroll
@@ -1254,6 +1268,12 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_step(Table<T> tb)
 // NTAP extends the hint to the L(p^l) loads: set when the solve's k + 1
 // images of A p do not fit the cache anyway (otherwise the next dots pass
 // finds them there).
+//
+// Bound by memory.  On 512 x 256 x 64 at k = 4, in FP64, this pass takes 82.0
+// us against 100.4 with stored directions; the dots and column passes 49.7 and
+// 45.3 against 46.2 and 42.8, since e now goes to k + 2 buffers in turn and
+// the cache absorbs fewer of its writes (a solve 72.5 -> 68.0 ms; binary32
+// vectors 1.10x).
 template <typename T, int KC, bool NTAP, int MESH>
 __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init)
 {
@@ -2155,7 +2175,9 @@ __global__ __launch_bounds__(RED_THREADS) void k_gm_restart(const GmInst* gi)
 // rather than one each.
 // NT: the Arnoldi vectors are loaded with the non-temporal hint (nt_ap_hint:
 // the cycle's vectors do not fit the Infinity Cache, which is then left to
-// z_j, w and v_{j+1}, read again within the step).
+// z_j, w and v_{j+1}, read again within the step: FT-GMRES(16) on 512 x 256 x
+// 64 308.6 -> 271.5 ms, the stencil pass 150 -> 130 us, orthogonalisation 124
+// -> 108, column solve 44 -> 36).
 template <bool NT>
 __device__ __forceinline__ double gm_load(const double* p)
 {

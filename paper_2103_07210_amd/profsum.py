@@ -105,7 +105,7 @@ def pmc(fetch_dir, write_dir, grid, cmd):
     print("\nEvery FP64 step kernel, scaled bytes per launch (launches that moved more than 1 MiB):\n")
     print("| kernel | launches | fetch MB | write MB | total MB |")
     print("|---|---|---|---|---|")
-    for key in ("k_update_thomas_full<double", "k_update_thomas<double", "k_stencil_dots<double",
+    for key in ("k_update_thomas<double", "k_stencil_dots<double",
                 "k_dir_update<double"):
         fk, n1 = avg_big(pick(fetch, key))
         wk, n2 = avg_big(pick(write, key))
