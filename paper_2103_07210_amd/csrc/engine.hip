@@ -184,13 +184,20 @@ int tuned_levels(const ftgcr_handle* h) { return tuned_for(h).kc; }
 
 // Levels per stencil block: as many as keep >= 1024 blocks in flight (8 at
 // most: deeper chunks raise register pressure more than they save halo).
-int auto_levels_per_block(int tx, int ty, int nz)
+// On the octahedral mesh the dots pass at 8 levels holds 181 registers, two
+// waves per SIMD, against four waves at 4, and a point's tables are read once
+// per 8 levels instead of 4: the waves win on a grid of a few rounds of the
+// chip, the reads on a larger one.  Microseconds a step at 4 and 8 levels,
+// FP64 and binary32 (blocks at 8 levels): O110 x 40 (1025) 75.6, 78.8 and
+// 54.9, 56.0; O160 x 51 (2961) 169.3, 170.3 and 92.9, 94.8; O200 x 51 (4578)
+// 271.9, 273.0 and 142.1, 138.1; O320 x 51 (11396) 693, 689 and 373, 359.
+int auto_levels_per_block(int mesh, int tx, int ty, int nz)
 {
     const long long cols = (long long)tx * ty;
     const int cand[] = {8, 4, 2};
     for (int kc : cand) {
         const long long blocks = cols * ((nz + kc - 1) / kc);
-        if (blocks >= 1024 && kc <= nz) return kc;
+        if (blocks >= (mesh == FTGCR_MESH_OCTAHEDRAL && kc == 8 ? 4096 : 1024) && kc <= nz) return kc;
     }
     return 1;
 }
@@ -220,7 +227,7 @@ void set_tiling(ftgcr_handle* h)
     }
     int kc = h->opt.levels_per_block;
     if (kc != 1 && kc != 2 && kc != 4 && kc != 8 && kc != 16) kc = h->tuned_kc ? h->tuned_kc : tuned_levels(h);
-    if (kc != 1 && kc != 2 && kc != 4 && kc != 8 && kc != 16) kc = auto_levels_per_block(h->tx, h->ty, g.nz);
+    if (kc != 1 && kc != 2 && kc != 4 && kc != 8 && kc != 16) kc = auto_levels_per_block(g.mesh, h->tx, h->ty, g.nz);
     h->kc = kc;
     h->tz = (g.nz + kc - 1) / kc;
     h->nblk_st = h->tx * h->ty * h->tz;
