@@ -92,3 +92,20 @@ def test_gmres_beyond_the_cache(ft, oracle_mod):
     assert _decisions(st["log"]) == _decisions(logo)
     assert _rel(x.cpu().numpy(), xo) <= 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("levels", [0, 8])
+def test_octahedral_levels_per_block(ft, oracle_mod, levels):
+    """O_110 x 40 is the smallest mesh with enough blocks for 8 levels: 4 by
+    default, 8 where asked for; 12 steps (two cycles and a half) of either."""
+    print("[gpu-case] octahedral levels per block", levels, flush=True)
+    pb = OctProblem(110, 40)
+    rhs = I.rhs(pb, 5)
+    s = ft.Solver(pb, kmax=5, max_steps=12, levels_per_block=levels)
+    assert s.tiling()["levels_per_block"] == (levels or 4)
+    x, st = s.solve(rhs, tol=1e-10, k=5)
+    xo, so, logo, _ = oracle_mod.OctOracle(pb).solve(rhs, tol=1e-10, k=5, max_steps=12)
+    assert st["steps_executed"] == so["steps_executed"] == 12
+    assert _decisions(st["log"]) == _decisions(logo)
+    assert _rel(x.cpu().numpy(), xo) <= 1e-10
+    s.close()
