@@ -641,6 +641,8 @@ struct DevEvent {
 
 // Steps a resident launch runs at most before the host looks at the state.
 constexpr long long RES_STEPS = 4096;
+// Rounds of launches a batch takes without progress (5 s each at most)
+constexpr int RES_LATE_MAX = 12;
 
 const char* const kKernelNames[3] = {"update_thomas", "stencil_dots", "dir_update"};
 
@@ -810,10 +812,11 @@ struct Runner {
         double rr_prev = -1.0;
         long long s_prev = 0;
         bool resident_norms = false;   // the state's norms are the resident kernel's
+        bool late = false;             // its blocks did not start together: this solve streams
         while (true) {
             while (evp < evs.size() && evs[evp].step <= launched) ++evp;
             const bool event_now = evp < evs.size() && evs[evp].step == launched + 1;
-            bool resident = use_resident(h);
+            bool resident = use_resident(h) && !late;
             if (event_now && resident) {
                 // events at the start of a step come between two launches of
                 // the resident kernel; one inside a step (e), or one on r
@@ -849,7 +852,6 @@ struct Runner {
                     h->res_waves = 0;
                     continue;
                 }
-                resident_norms = true;
                 launched += cnt;
                 issued += cnt;
             } else {
@@ -868,13 +870,21 @@ struct Runner {
             int status = RUNNING;
             ftgcr_status rc = read_status(&status);
             if (rc != FTGCR_OK) return rc;
+            if (h->st_host->res_fail == RES_BROKEN)
+                return fail(h, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
+            if (h->st_host->res_fail == RES_LATE) {   // nothing has changed since the last read
+                L::resident_late(tb, s);
+                late = true;
+                launched = h->st_host->s;
+                continue;
+            }
+            resident_norms = resident_norms || resident;
             if (resident) {
                 for (int q = 0; q < 3; ++q) {
                     h->kt_ms[q] += 1e-5 * (double)h->st_host->res_ticks[q];
                     h->kt_n[q] += h->st_host->res_counts[q];
                 }
             }
-            if (h->st_host->res_fail) return fail(h, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
             if (status != RUNNING) return FTGCR_OK;
             if (issued > guard) return fail(h, FTGCR_E_HIP, "step loop did not terminate");
             const SolveState& hs = *h->st_host;
@@ -1423,21 +1433,29 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
     std::vector<size_t> evp(n, 0);
     std::vector<char> resident_norms(n, 0);   // the member's state holds the resident kernel's norms
     std::vector<long long> host(2 * n), before(n, -1);
-    std::vector<char> launched(n, 0);
+    std::vector<char> launched(n, 0), norms_before(n, 0);
+    int late = 0;   // rounds of launches in which a member's blocks did not start together
     while (true) {
         L::gather_status(tb_all, status, s);
         HIP_TRY(h0, hipMemcpyAsync(host.data(), status, 2 * n * sizeof(long long), hipMemcpyDeviceToHost, s));
         HIP_TRY(h0, hipStreamSynchronize(s));
-        bool any = false, ahead = false;
+        bool any = false, ahead = false, again = false;
         for (int m = 0; m < n; ++m) {
+            if (host[2 * m] == BROKEN) return fail(h0, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
             if (host[2 * m] != RUNNING) continue;
             any = true;
-            if (launched[m] && host[2 * m + 1] <= before[m])
-                return fail(h0, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
+            if (launched[m] && host[2 * m + 1] <= before[m]) {   // nothing of it has changed
+                resident_norms[m] = norms_before[m];
+                again = true;
+            }
             while (evp[m] < evs[m].size() && evs[m][evp[m]].step <= host[2 * m + 1]) ++evp[m];
             ahead = ahead || evp[m] < evs[m].size();
         }
         if (!any) return FTGCR_OK;
+        if (again) {
+            if (++late > RES_LATE_MAX) return fail(h0, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
+            L::resident_late(tb_all, s);
+        }
         std::fill(launched.begin(), launched.end(), 0);
         std::vector<Inst<double>> act;
         std::vector<int> pre;
@@ -1486,6 +1504,7 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
                 in.res_new_norms = resident_norms[m] ? 0 : 1;
                 in.res_stop = next - 1 + RES_STEPS;
                 if (evp[m] < evs[m].size()) in.res_stop = std::min<long long>(in.res_stop, evs[m][evp[m]].step - 1);
+                norms_before[m] = resident_norms[m];
                 resident_norms[m] = 1;
                 before[m] = next - 1;
                 launched[m] = 1;

@@ -61,7 +61,7 @@ struct DetectRec {
 // Per-solve control state (device memory, written by single-thread kernel
 // sections only).
 struct SolveState {
-    int res_fail;        // 1: a resident kernel's block waited in vain (never stored back from a copy)
+    int res_fail;        // RES_LATE, RES_BROKEN: a resident kernel's block waited in vain
     unsigned res_seq;    // rounds of exchanges the resident kernels of this handle have run
     unsigned long long res_ticks[3];   // the last resident launch's timed rounds (100 MHz)
     int res_counts[3], res_pad;
@@ -263,6 +263,11 @@ constexpr int RES_BLOCKS = 256;
 // tagged words a value
 constexpr int RES_COPIES = 4;
 constexpr size_t RES_WORDS = 2 * (size_t)RES_COPIES * NV_MAX * RES_BLOCKS * 2;
+// SolveState::res_fail: a launch whose blocks did not all start in time has
+// changed nothing but its exchange words; one that came apart later has
+// broken the solve (gather_status then reports BROKEN for its status)
+enum { RES_LATE = 1, RES_BROKEN = 2 };
+constexpr int BROKEN = -2;
 
 // Wavefronts per block with which the resident kernel takes a problem of
 // half columns of depth H on at most `cus` blocks (0: it does not), and its
@@ -303,6 +308,8 @@ template <typename T> struct Launch {
     static void finish_step(const Table<T>& tb, hipStream_t s);   // finish_col + finish_alpha
     static void finish_alpha(const Table<T>& tb, hipStream_t s);
     static void finish_beta(const Table<T>& tb, int init, hipStream_t s);
+    // after a resident launch that ended RES_LATE: before the next one
+    static void resident_late(const Table<T>& tb, hipStream_t s);
     // nt_ap: load the L(p^l) with the non-temporal hint (nt_ap_hint)
     static void dir_update(const Table<T>& tb, int total_st_blocks, int kc, int init, bool nt_ap, hipStream_t s,
                            hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);

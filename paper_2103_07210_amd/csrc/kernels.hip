@@ -1958,8 +1958,26 @@ __global__ void k_gather_status(Table<T> tb, long long* out)
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= tb.n) return;
     const SolveState* st = tb.inst[m].st;
-    out[2 * m] = st->status;
+    out[2 * m] = st->res_fail == RES_BROKEN ? BROKEN : st->status;
     out[2 * m + 1] = st->s;
+}
+
+// Clears RES_LATE and leaves the words of that launch's round behind.
+template <typename T>
+__global__ void k_resident_late(Table<T> tb)
+{
+    const int m = blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= tb.n) return;
+    SolveState* st = tb.inst[m].st;
+    if (st->res_fail != RES_LATE) return;
+    st->res_fail = 0;
+    st->res_seq += 2;
+}
+
+template <typename T>
+void Launch<T>::resident_late(const Table<T>& tb, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_resident_late<T>, dim3((tb.n + 63) / 64), dim3(64), 0, s, tb);
 }
 
 template <typename T>

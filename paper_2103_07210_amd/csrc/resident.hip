@@ -36,7 +36,10 @@
 //
 // All blocks of a launch have to run at once: the launch is cooperative, one
 // block per CU at most, and every wait is bounded (a wait that ends in vain
-// sets SolveState::res_fail and the block leaves).
+// sets SolveState::res_fail and the block leaves).  The first exchange comes
+// before any vector is written: where another stream's work keeps blocks from
+// starting that long, the launch ends with the solve as it was (RES_LATE) and
+// the host goes on in the streaming kernels (a batch: launches again).
 #include <algorithm>
 
 #include "device.h"
@@ -385,8 +388,8 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         __syncthreads();
         return true;
     };
-    auto gave_up = [&]() {
-        if (tid == 0) as_global_mut(gst)->res_fail = 1;
+    auto gave_up = [&](int how) {   // (its result awaited: blocks that start later see it)
+        if (tid == 0 && atomicMax(&gst->res_fail, how) > RES_BROKEN) s_fail = 1;
     };
     auto decide = [&](double rn, double rs) {   // thread 0, on this block's copy of the state
         decide_step(&s_st, log, rn, rs, hist, hist_cap);
@@ -408,28 +411,39 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         if (lane == 0) s_wp[q][w] = v;
     };
 
-    // the detector compares norms of r summed in one order: these two (of r and
-    // of the backup's) come from the streaming kernels
-    if ((arg.s_stop < 0 ? in.res_new_norms : arg.new_norms) && s_st.status == RUNNING) {
-        const T* rp = uniform(s_R[s_st.r_bak]);
-        double a0 = 0.0, a1 = 0.0;
+    // The first exchange, before anything is written.  The detector compares
+    // norms of r summed in one order: where these two (of r and of the backup's)
+    // come from the streaming kernels, they are formed anew here.
+    if (s_st.status == RUNNING) {
+        const bool norms = (arg.s_stop < 0 ? in.res_new_norms : arg.new_norms) != 0;
+        if (norms) {
+            const T* rp = uniform(s_R[s_st.r_bak]);
+            double a0 = 0.0, a1 = 0.0;
 #pragma unroll
-        for (int q = 0; q < H; ++q) {
-            a0 = fma((double)r[q], (double)r[q], a0);
-            const double b = q >= H - nmine ? (double)far_load(rp, at[q]) : 0.0;
-            a1 = fma(b, b, a1);
-            settle(a0);
-            settle(a1);
+            for (int q = 0; q < H; ++q) {
+                a0 = fma((double)r[q], (double)r[q], a0);
+                const double b = q >= H - nmine ? (double)far_load(rp, at[q]) : 0.0;
+                a1 = fma(b, b, a1);
+                settle(a0);
+                settle(a1);
+            }
+            partial(0, a0);
+            partial(1, a1);
+        } else {
+            partial(0, 0.0);
         }
-        partial(0, a0);
-        partial(1, a1);
-        publish(2);
-        if (!collect(2)) return gave_up();
+        publish(norms ? 2 : 1);
+        if (!collect(norms ? 2 : 1)) return gave_up(RES_LATE);
         if (tid == 0) {
-            s_st.rr_old = s_sum[0];
-            s_st.b_rr = s_sum[1];
+            if (norms) {
+                s_st.rr_old = s_sum[0];
+                s_st.b_rr = s_sum[1];
+            }
+            // blocks that gave up before this one started left their words behind
+            if (__hip_atomic_load(as_global(&gst->res_fail), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) s_fail = 1;
         }
         __syncthreads();
+        if (s_fail) return;
     }
 
     // kernel timing (options.profile_kernels): the three rounds' durations on
@@ -537,7 +551,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
                 for (int q = 0; q < H; ++q) *elem_mut(ub, at[q]) = e[q];
             }
         }
-        if (!collect(2)) return gave_up();
+        if (!collect(2)) return gave_up(RES_BROKEN);
         const double rn = s_sum[0], rs = s_sum[1];
         timed(0, step);
 
@@ -680,7 +694,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         }
         publish(nu + 1);
         if (tid == 0) decide(rn, rs);   // while the products travel
-        if (!collect(nu + 1)) return gave_up();
+        if (!collect(nu + 1)) return gave_up(RES_BROKEN);
         timed(1, step);
         if (s_st.status != RUNNING || !s_st.active) {
             if (s_st.status == RUNNING) load_state();   // rolled back: the restored r and L(p^0)
@@ -786,7 +800,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         }
         __syncthreads();   // bm, xc and the bases are read before the slots move
         if (tid == 0) next_pass(&s_st);
-        if (!collect(2)) return gave_up();
+        if (!collect(2)) return gave_up(RES_BROKEN);
         if (tid == 0) {
             s_st.beta_num = s_sum[0];
             s_st.d_cur = s_sum[1];
@@ -805,6 +819,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         __syncthreads();
         if (tid == 0) {
             s_st.res_seq = seq;
+            s_st.res_fail = __hip_atomic_load(as_global(&gst->res_fail), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             for (int q = 0; q < 3; ++q) {
                 s_st.res_ticks[q] = ticks[q];
                 s_st.res_counts[q] = counts[q];

@@ -114,3 +114,57 @@ def test_kernel_times_cover_the_steps(ft):
     s.close()
     assert kt["update_thomas"][0] == st["steps_executed"]
     assert 0 < sum(v[1] for v in kt.values()) <= st["time_ms"]
+
+
+def test_two_threads_and_a_busy_stream(ft):
+    """Two threads, each with its own handle and stream, on grids that take a
+    block on every CU, beside a stream of large copies: launches wait for
+    one another's blocks to leave, and every solve is the lone solve's, to the
+    last bit."""
+    import threading
+
+    import torch
+    pbs = [Problem(256, 128, 32), Problem(250, 120, 31, hill_lon=1.0)]
+    rhs = [I.rhs(pb, 60 + m) for m, pb in enumerate(pbs)]
+    alone = []
+    for pb, b in zip(pbs, rhs):
+        s = ft.Solver(pb, kmax=3)
+        alone.append(s.solve(b, tol=1e-8, k=3))
+        s.close()
+    out, errors = [[], []], []
+
+    def work(m):
+        try:
+            torch.cuda.set_device(0)
+            st = torch.cuda.Stream()
+            with torch.cuda.stream(st):
+                s = ft.Solver(pbs[m], kmax=3)
+                for rep in range(4):
+                    print("[gpu-case] thread", m, "solve", rep, flush=True)
+                    x, stats = s.solve(rhs[m], tol=1e-8, k=3)
+                    out[m].append((x.clone(), stats))
+                st.synchronize()
+                s.close()
+        except Exception as e:   # noqa: BLE001 (reported by the main thread)
+            errors.append(e)
+
+    a = torch.ones(1 << 27, device="cuda")
+    b = torch.empty_like(a)
+    busy = torch.cuda.Stream()
+    busy.wait_stream(torch.cuda.current_stream())
+    threads = [threading.Thread(target=work, args=(m,)) for m in range(2)]
+    for t in threads:
+        t.start()
+    with torch.cuda.stream(busy):
+        for _ in range(200):
+            b.copy_(a)
+    for t in threads:
+        t.join(100)
+        assert not t.is_alive()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for m in range(2):
+        assert len(out[m]) == 4
+        for x, stats in out[m]:
+            assert stats["steps_executed"] == alone[m][1]["steps_executed"]
+            assert torch.equal(x, alone[m][0])
