@@ -91,6 +91,7 @@ struct ftgcr_handle {
     unsigned long long* xw = nullptr;
 
     int nblk_col = 0, nblk_st = 0, nblk_dir = 0;
+    int fold_st = 0, fold_dir = 0;   // Inst's
     int kc = 1, tx = 1, ty = 1, tz = 1, H = 4, kc_dir = 1, tz_dir = 1;
     int tuned_kc = 0;   // from ftgcr_autotune (0: none)
     // block orders (ORD_*) of the stencil and direction grids, and
@@ -182,6 +183,8 @@ Tuned tuned_for(const ftgcr_handle* h)
 
 int tuned_levels(const ftgcr_handle* h) { return tuned_for(h).kc; }
 
+long long part_stride(const ftgcr_handle* h);
+
 // Levels per stencil block: as many as keep >= 1024 blocks in flight (8 at
 // most: deeper chunks raise register pressure more than they save halo).
 // On the octahedral mesh the dots pass at 8 levels holds 181 registers, two
@@ -232,6 +235,9 @@ void set_tiling(ftgcr_handle* h)
     h->tz = (g.nz + kc - 1) / kc;
     h->nblk_st = h->tx * h->ty * h->tz;
     dir_tiling(kc, g.nz, h->tx, h->ty, h->kc_dir, h->tz_dir, h->nblk_dir);
+    auto fold = [&](int nblk) { return nblk > FOLD_BLOCKS && nblk + RED_FOLD <= part_stride(h) ? RED_FOLD : 0; };
+    h->fold_st = fold(h->nblk_st);
+    h->fold_dir = fold(h->nblk_dir);
     // block orders: the option, else the tuned choice, else the mesh's
     // default (octahedral: XCD-aware level chunks in a row, measured 18%
     // faster on O160 x 51 than tiles in a row, its slot tables and neighbour
@@ -306,6 +312,8 @@ Inst<T> make_inst(const ftgcr_handle* h, const double* rhs, double* x, void* ws)
     in.nblk_dir = h->nblk_dir;
     in.kc_dir = h->kc_dir;
     in.tz_dir = h->tz_dir;
+    in.fold_st = h->fold_st;
+    in.fold_dir = h->fold_dir;
     in.ord_st = h->ord_st;
     in.ord_dir = h->ord_dir;
     in.xw = h->xw;
@@ -744,13 +752,16 @@ struct Runner {
             L::finish_col(tb, 0, s);
             for (const DevEvent* ev : *mid) event(*ev);
             timed(1, [&](hipEvent_t a, hipEvent_t b) { L::stencil_dots(tb, h->nblk_st, h->kc, 0, s, a, b); });
+            if (h->fold_st) L::fold(tb, 0, h->fold_st, h->kmax, s);
             L::finish_alpha(tb, s);
         } else {
             // dots pass first, then decision and alpha in one launch
             timed(1, [&](hipEvent_t a, hipEvent_t b) { L::stencil_dots(tb, h->nblk_st, h->kc, 1, s, a, b); });
+            if (h->fold_st) L::fold(tb, 0, h->fold_st, h->kmax, s);
             L::finish_step(tb, s);
         }
         timed(2, [&](hipEvent_t a, hipEvent_t b) { L::dir_update(tb, h->nblk_dir, h->kc_dir, 0, h->nt_ap, s, a, b); });
+        if (h->fold_dir) L::fold(tb, 1, h->fold_dir, 2, s);
         L::finish_beta(tb, 0, s);
     }
 
@@ -759,6 +770,7 @@ struct Runner {
         L::update_thomas(tb, h->nblk_col, h->H, 1, s);
         L::finish_col(tb, 1, s);
         L::dir_update(tb, h->nblk_dir, h->kc_dir, 1, h->nt_ap, s);
+        if (h->fold_dir) L::fold(tb, 1, h->fold_dir, 2, s);
         L::finish_beta(tb, 1, s);
     }
 
@@ -1583,6 +1595,7 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
     for (int m = 0; m < n; ++m) {
         ftgcr_handle* h = hs[m];
         ins[m] = make_inst<double>(h, rhs[m], x[m], h->ws);
+        ins[m].fold_st = ins[m].fold_dir = 0;
         ins[m].kc = kc;
         ins[m].tz = (h->geo.nz + kc - 1) / kc;
         ins[m].nblk_st = ins[m].tx * ins[m].ty * ins[m].tz;

@@ -39,6 +39,9 @@ constexpr int ST_TX = 64;
 constexpr int ST_TY = 4;
 constexpr int ST_THREADS = ST_TX * ST_TY;
 constexpr int RED_THREADS = 1024;
+// Partials per value after folding, and the blocks beyond which it pays
+constexpr int RED_FOLD = 32;
+constexpr int FOLD_BLOCKS = 16384;
 // Octahedral mesh: neighbour slots per point (the triangulation's valence
 // is at most 6); a block of the stencil kernels covers ST_THREADS
 // consecutive points.
@@ -180,6 +183,9 @@ struct Inst {
     // the direction pass (the most registers per level) has its own level
     // tiling over the same columns
     int nblk_dir, kc_dir, tz_dir;
+    // partials per value that the two grids' are folded to before the one-block
+    // reductions (0: they read the blocks' own)
+    int fold_st, fold_dir;
     // block orders (ORD_*) of the stencil grid and of the direction grid
     int ord_st, ord_dir;
     // the resident kernel's exchange words, blocks and tiles in x
@@ -308,6 +314,7 @@ template <typename T> struct Launch {
     static void finish_step(const Table<T>& tb, hipStream_t s);   // finish_col + finish_alpha
     static void finish_alpha(const Table<T>& tb, hipStream_t s);
     static void finish_beta(const Table<T>& tb, int init, hipStream_t s);
+    static void fold(const Table<T>& tb, int dir, int parts, int values, hipStream_t s);
     // after a resident launch that ended RES_LATE: before the next one
     static void resident_late(const Table<T>& tb, hipStream_t s);
     // nt_ap: load the L(p^l) with the non-temporal hint (nt_ap_hint)

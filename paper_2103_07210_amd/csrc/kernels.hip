@@ -51,13 +51,15 @@ enum { GM_INIT = 0, GM_CHECK = 1, GM_REDO = 2 };
 // order of the additions is the same for every (G, U).  The returned LDS
 // array holds the nv sums; out, if not null, gets the first two of them in
 // registers.  Both are valid in every thread.
+// `first`: the first partial's place in its row.
 template <int G, int U, typename I>
-__device__ __forceinline__ const double* sum_partials(const I& in, int nblk, int row0, int nv, double* out)
+__device__ __forceinline__ const double* sum_partials(const I& in, int nblk, int row0, int nv, double* out,
+                                                      int first = 0)
 {
     constexpr int NW = RED_THREADS / 64;
     __shared__ double sh[NV_MAX][NW];
     __shared__ double res[NV_MAX];
-    const gptr<double> part = as_global(in.part);
+    const gptr<double> part = as_global(in.part) + first;
     const long long stride = in.pstride;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int q0 = 0; q0 < nv; q0 += G) {
@@ -1201,6 +1203,42 @@ __global__ __launch_bounds__(ST_THREADS) void k_stencil_dots(Table<T> tb, int sp
     }
 }
 
+// The partials of a large grid's dots (dir = 0) or direction pass (1) to
+// RED_FOLD per value, kept behind them in their rows, before the one-block
+// reduction: one CU takes in about 42 GB/s of partials, whatever it keeps in
+// flight.  On 1024 x 512 x 96 (24576 and 49152 blocks) the two reductions take
+// 10 us and this 9, against 35 in one block each (a step 1206 -> 1186 us, in
+// binary32 685 -> 667); on 1024 x 512 x 36 (18432 blocks in the direction pass
+// alone) a step 483.6 -> 481.2.
+// Block (x, y): part x of value y.
+template <typename T>
+__global__ __launch_bounds__(ST_THREADS) void k_fold(Table<T> tb, int dir)
+{
+    __shared__ double sh[4];
+    const Inst<T>& in = tb.inst[0];
+    const SolveState* st = in.st;
+    if (st->status != RUNNING) return;
+    const int nblk = dir ? in.nblk_dir : in.nblk_st, parts = dir ? in.fold_dir : in.fold_st;
+    const int q = blockIdx.y;
+    if (q >= (dir ? 2 : st->nu + 1)) return;
+    double* row = in.part + (long long)((dir ? 0 : DOT_ROW0) + q) * in.pstride;
+    const gptr<double> from = as_global((const double*)row);
+    const int per = (nblk + parts - 1) / parts;
+    const int b1 = min(nblk, ((int)blockIdx.x + 1) * per);
+    double acc = 0.0;
+    constexpr int U = 4;
+    for (int b = blockIdx.x * per + threadIdx.x; b < b1; b += U * ST_THREADS) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = b + u * ST_THREADS < b1 ? from[b + u * ST_THREADS] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (b + u * ST_THREADS < b1) acc += v[u];
+    }
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0) row[nblk + blockIdx.x] = acc;
+}
+
 // alpha_l = -<L(e), L(p^l)> / <L(p^l), L(p^l)>, the new direction over the
 // basis (p^{nu+1} = e + sum_l alpha_l p^l), at a cycle's end the iterate
 // update over the basis, and the iterate buffer the direction pass writes;
@@ -1209,7 +1247,8 @@ template <typename T>
 __device__ __forceinline__ void finish_alpha_body(const Inst<T>& in, SolveState* st)
 {
     const int nu = st->nu;
-    const double* v = sum_partials<4, 4>(in, in.nblk_st, DOT_ROW0, nu + 1, nullptr);
+    const double* v = sum_partials<4, 4>(in, in.fold_st ? in.fold_st : in.nblk_st, DOT_ROW0, nu + 1, nullptr,
+                                         in.fold_st ? in.nblk_st : 0);
     if ((int)threadIdx.x <= nu) st->alpha[threadIdx.x] = -v[threadIdx.x] / st->d[threadIdx.x];
     __syncthreads();
     basis_row(st, nu, threadIdx.x);
@@ -1445,7 +1484,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_beta(Table<T> tb, int in
     const long long word = state_word_load(gst);
     const int status = gst->status, active = gst->active;   // not the staged ones: see k_finish_step
     double v[2];
-    sum_partials<2, 8>(in, in.nblk_dir, 0, 2, v);
+    sum_partials<2, 8>(in, in.fold_dir ? in.fold_dir : in.nblk_dir, 0, 2, v, in.fold_dir ? in.nblk_dir : 0);
     state_word_stage(&s_st, word);
     __syncthreads();
     SolveState* st = &s_st;
@@ -1837,6 +1876,12 @@ template <typename T>
 void Launch<T>::finish_alpha(const Table<T>& tb, hipStream_t s)
 {
     hipLaunchKernelGGL(k_finish_alpha<T>, dim3(tb.n), dim3(RED_THREADS), 0, s, tb);
+}
+
+template <typename T>
+void Launch<T>::fold(const Table<T>& tb, int dir, int parts, int values, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fold<T>, dim3(parts, values), dim3(ST_THREADS), 0, s, tb, dir);
 }
 
 template <typename T>

@@ -109,3 +109,21 @@ def test_octahedral_levels_per_block(ft, oracle_mod, levels):
     assert _decisions(st["log"]) == _decisions(logo)
     assert _rel(x.cpu().numpy(), xo) <= 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("ny,nz", [(2048, 64), (2052, 64), (2056, 63)])
+@pytest.mark.parametrize("k", [4, 16])
+def test_folded_partials(ft, oracle_mod, ny, nz, k):
+    """16384 stencil blocks (reduced by one block each) and 16416 and 16448
+    (folded first): 20 steps, one of them with a flip in e."""
+    print("[gpu-case] folded partials", ny, nz, k, flush=True)
+    pb = Problem(3, ny, nz, hill_amp=0.6)
+    rhs = I.rhs(pb, 9)
+    plan = [FaultEvent(6, "e", 62, idx=np.array([pb.n // 2]))]
+    s = ft.Solver(pb, kmax=k, max_steps=20, levels_per_block=2)
+    x, st = s.solve(rhs, tol=1e-13, k=k, plan=plan)
+    xo, so, logo, _ = oracle_mod.Oracle(pb).solve(rhs, tol=1e-13, k=k, plan=plan, max_steps=20)
+    assert st["steps_executed"] == so["steps_executed"] == 20
+    assert _decisions(st["log"]) == _decisions(logo)
+    assert _rel(x.cpu().numpy(), xo) <= 1e-10
+    s.close()
