@@ -101,6 +101,13 @@ __device__ __forceinline__ double block_sum(double v, double* sh)
     return ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
+// Most empty rows of a half column in the template of depth H (the next
+// smaller depth holds anything shorter).
+constexpr int pad_rows(int H)
+{
+    return H == 4 ? 4 : H == 8 ? 5 : H == 16 ? 9 : H == 24 ? 9 : H == 28 ? 5 : H == 32 ? 5 : 9;
+}
+
 // Per-column constants: hill_amp * h at the five horizontal positions and
 // the metric factors of the faces.
 struct ColW {

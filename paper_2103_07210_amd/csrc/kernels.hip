@@ -565,13 +565,6 @@ __global__ __launch_bounds__(RED_THREADS) void k_finish_residual(Table<T> tb, in
 // fill their template take no longer per byte: O160 x 51 41.8 -> 33.3 us,
 // 700 x 333 x 47 83.6 -> 74.5 us against a guard on every row.
 
-// Most empty rows of a half column in the template of depth H (the next
-// smaller depth holds anything shorter).
-constexpr int pad_rows(int H)
-{
-    return H == 4 ? 4 : H == 8 ? 5 : H == 16 ? 9 : H == 24 ? 9 : H == 28 ? 5 : H == 32 ? 5 : 9;
-}
-
 // MODE_GM (FT-GMRES, FP64): the current Arnoldi vector U[j] is divided by
 // den[j] (normalised, written back in place) and z_j = P^{-1} v_j goes to
 // Z[j]; no norms.

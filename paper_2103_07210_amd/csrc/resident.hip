@@ -790,9 +790,12 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
                 if (stores) {
 #pragma unroll
                     for (int c = 0; c < CL; ++c) {
-                        // (an empty row would leave 0 at the first level: that
-                        // level's own row comes later)
-                        *elem_mut(pout, at[c0 + c]) = (T)p[c];
+                        // (xo may be xb: a level is updated by its own row
+                        // alone, an empty row of an earlier chunk would add
+                        // its increment once more)
+                        const int q = c0 + c;
+                        if (q < pad_rows(H) && q < H - nmine) continue;
+                        *elem_mut(pout, at[q]) = (T)p[c];
                         *elem_mut(xo, ax[c]) = x[c];
                     }
                 }
