@@ -415,6 +415,20 @@ const char* ftgcr_last_error(const ftgcr_handle* h);
 ftgcr_status ftgcr_debug_apply_A(ftgcr_handle* h, const double* in_dev, double* out_dev);
 ftgcr_status ftgcr_debug_apply_Pinv(ftgcr_handle* h, const double* in_dev, double* out_dev);
 
+/* Test entry of the cases in which a launch that runs many steps (see
+ * options.levels_per_block) does not do so: from this handle's `launch`-th such
+ * launch on (1: its next one; 0: none), they end as if
+ *   LATE     their blocks had not started together (nothing is changed; the
+ *            steps go on in the streaming kernels);
+ *   BROKEN   they had come apart after their last step (the solve fails with
+ *            E_HIP, a later one on the handle starts afresh);
+ *   REFUSED  the device did not take the launch (as LATE).
+ * All blocks leave by the same exits as in those cases.  In a batch BROKEN and
+ * LATE hold for the member with this handle, REFUSED for the whole launch.
+ * E_INVALID for other arguments. */
+enum { FTGCR_RESIDENT_LATE = 1, FTGCR_RESIDENT_BROKEN = 2, FTGCR_RESIDENT_REFUSED = 3 };
+ftgcr_status ftgcr_debug_resident(ftgcr_handle* h, int32_t launch, int32_t outcome);
+
 #ifdef __cplusplus
 }
 #endif

@@ -89,6 +89,7 @@ struct ftgcr_handle {
     int cus = 0;              // of the device
     bool no_resident = false; // a tuner is timing the streaming kernels
     unsigned long long* xw = nullptr;
+    int test_launch = 0, test_outcome = 0;   // ftgcr_debug_resident
 
     int nblk_col = 0, nblk_st = 0, nblk_dir = 0;
     int fold_st = 0, fold_dir = 0;   // Inst's
@@ -346,6 +347,16 @@ bool use_resident(const ftgcr_handle* h)
 {
     return h->res_waves > 0 && !h->no_resident && h->opt.levels_per_block == 0 && h->opt.order_stencil == FTGCR_ORDER_AUTO &&
            h->opt.order_dir == FTGCR_ORDER_AUTO;
+}
+
+// What this handle's next resident launch is made to end as (0: nothing).
+int forced_outcome(ftgcr_handle* h)
+{
+    if (h->test_launch > 1) {
+        h->test_launch -= 1;
+        return 0;
+    }
+    return h->test_launch == 1 ? h->test_outcome : 0;
 }
 
 // options.profile_kernels, bits 0-7: 1 times all three step kernels, any
@@ -682,6 +693,36 @@ void collect_times(ftgcr_handle* h, long long last_step)
 }
 
 template <typename T>
+void inject_event(const Table<T>& tb, const DevEvent& ev, long long n, hipStream_t s)
+{
+    using L = Launch<T>;
+    L::event_prep(tb, ev.vec, s);
+    if (ev.vec != FTGCR_V_E) L::event_copy(tb, (int)std::min<long long>((n + 255) / 256, 8192), s);
+    L::event_inject(tb, (int)std::max<long long>(1, std::min<long long>((ev.count + 255) / 256, 8192)), ev.idx, ev.bits,
+                    ev.count, ev.start, ev.bit, false, s);
+}
+
+// The state's norms in the streaming kernels' order, after a resident launch
+// that did not run.  on_r: this step's events on r, already injected: they are
+// taken out meanwhile (a flip is its own inverse), since the detector compares
+// with the norm of r before them.
+template <typename T>
+void streaming_norms(const Table<T>& tb, const std::vector<const DevEvent*>& on_r, int nblk_col, int H, hipStream_t s)
+{
+    using L = Launch<T>;
+    auto flip = [&]() {
+        for (const DevEvent* ev : on_r) {
+            L::event_prep(tb, FTGCR_V_R, s);   // (r is no longer in the backup's buffer: no copy)
+            L::event_inject(tb, (int)std::max<long long>(1, std::min<long long>((ev->count + 255) / 256, 8192)), ev->idx,
+                            ev->bits, ev->count, ev->start, ev->bit, true, s);
+        }
+    };
+    flip();
+    L::norms(tb, nblk_col, H, s);
+    flip();
+}
+
+template <typename T>
 struct Runner {
     using L = Launch<T>;
     ftgcr_handle* h;
@@ -776,12 +817,7 @@ struct Runner {
 
     void event(const DevEvent& ev)
     {
-        const long long n = h->geo.n;
-        const int gcopy = (int)std::min<long long>((n + 255) / 256, 8192);
-        const int ginj = (int)std::max<long long>(1, std::min<long long>((ev.count + 255) / 256, 8192));
-        L::event_prep(tb, ev.vec, s);
-        if (ev.vec != FTGCR_V_E) L::event_copy(tb, gcopy, s);
-        L::event_inject(tb, ginj, ev.idx, ev.bits, ev.count, ev.start, ev.bit, s);
+        inject_event<T>(tb, ev, h->geo.n, s);
         if (ev.vec == FTGCR_V_R || ev.vec == FTGCR_V_AP) {
             L::beta_dots(tb, h->nblk_st, s);
         }
@@ -825,6 +861,11 @@ struct Runner {
         long long s_prev = 0;
         bool resident_norms = false;   // the state's norms are the resident kernel's
         bool late = false;             // its blocks did not start together: this solve streams
+        std::vector<const DevEvent*> on_r;   // events on r before the launch
+        auto back_to_streaming = [&]() {     // the launch did not run
+            if (resident_norms) streaming_norms<T>(tb, on_r, h->nblk_col, h->H, s);
+            resident_norms = false;
+        };
         while (true) {
             while (evp < evs.size() && evs[evp].step <= launched) ++evp;
             const bool event_now = evp < evs.size() && evs[evp].step == launched + 1;
@@ -851,17 +892,25 @@ struct Runner {
                 launched += 1;
                 issued += 1;
             } else if (resident) {
-                for (; evp < evs.size() && evs[evp].step == launched + 1; ++evp) event(evs[evp]);
+                on_r.clear();
+                for (; evp < evs.size() && evs[evp].step == launched + 1; ++evp) {
+                    if (evs[evp].vec == FTGCR_V_R) on_r.push_back(&evs[evp]);
+                    event(evs[evp]);
+                }
                 // to the next event or the outcome, in one launch
                 long long cnt = RES_STEPS;
                 if (evp < evs.size()) cnt = std::min<long long>(cnt, evs[evp].step - 1 - launched);
+                const int forced = forced_outcome(h);
                 const ResidentArgs arg{launched + cnt, k + 1, resident_norms ? 0 : 1, noalloc ? 0 : profile_mask(h),
-                                       profile_stride(h)};
+                                       profile_stride(h), forced};
                 const hipError_t e =
-                    resident_run<T>(tb, h->blk0 + 6, h->nblk_res, h->geo.mesh, h->H, h->res_waves, arg, s);
+                    forced == FTGCR_RESIDENT_REFUSED
+                        ? hipErrorCooperativeLaunchTooLarge
+                        : resident_run<T>(tb, h->blk0 + 6, h->nblk_res, h->geo.mesh, h->H, h->res_waves, arg, s);
                 if (e != hipSuccess) {   // the device does not take the launch: the streaming kernels from here
                     (void)hipGetLastError();
                     h->res_waves = 0;
+                    back_to_streaming();
                     continue;
                 }
                 launched += cnt;
@@ -887,6 +936,7 @@ struct Runner {
             if (h->st_host->res_fail == RES_LATE) {   // nothing has changed since the last read
                 L::resident_late(tb, s);
                 late = true;
+                back_to_streaming();
                 launched = h->st_host->s;
                 continue;
             }
@@ -1514,6 +1564,7 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
                 in.rtx = rb.rtx[m];
                 in.nblk_res = rb.nblk[m];
                 in.res_new_norms = resident_norms[m] ? 0 : 1;
+                in.res_leave = forced_outcome(hs[m]);
                 in.res_stop = next - 1 + RES_STEPS;
                 if (evp[m] < evs[m].size()) in.res_stop = std::min<long long>(in.res_stop, evs[m][evp[m]].step - 1);
                 norms_before[m] = resident_norms[m];
@@ -1554,7 +1605,7 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
             t.inst = inst + go.at;
             t.n = go.count;
             HIP_TRY(h0, resident_run<double>(t, blk0 + go.first, go.blocks, h0->geo.mesh, go.d->H, go.d->waves,
-                                             ResidentArgs{-1, k + 1, 0, 0, 0}, s));
+                                             ResidentArgs{-1, k + 1, 0, 0, 0, 0}, s));
         }
         HIP_TRY(h0, hipStreamSynchronize(s));   // act and pre are read until here
     }
@@ -1647,11 +1698,7 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
     std::vector<long long> host_status(2 * n);
     auto apply = [&](int m, const DevEvent& ev) {
         const Table<double> t1 = single(m);
-        const long long nn = hs[m]->geo.n;
-        L::event_prep(t1, ev.vec, s);
-        if (ev.vec != FTGCR_V_E) L::event_copy(t1, (int)std::min<long long>((nn + 255) / 256, 8192), s);
-        L::event_inject(t1, (int)std::max<long long>(1, std::min<long long>((ev.count + 255) / 256, 8192)),
-                        ev.idx, ev.bits, ev.count, ev.start, ev.bit, s);
+        inject_event<double>(t1, ev, hs[m]->geo.n, s);
         if (ev.vec == FTGCR_V_R || ev.vec == FTGCR_V_AP) L::beta_dots(t1, ins[m].nblk_st, s);
     };
     const std::vector<std::pair<int, const DevEvent*>> no_mid;
@@ -2302,6 +2349,16 @@ ftgcr_status ftgcr_debug_apply_A(ftgcr_handle* h, const double* in_dev, double* 
     Launch<double>::debug_apply_A(tb, h->nblk_st, h->kc, in_dev, out_dev, h->stream);
     HIP_TRY(h, hipGetLastError());
     HIP_TRY(h, hipStreamSynchronize(h->stream));
+    return FTGCR_OK;
+}
+
+ftgcr_status ftgcr_debug_resident(ftgcr_handle* h, int32_t launch, int32_t outcome)
+{
+    if (!h) return FTGCR_E_INVALID;
+    if (launch < 0 || (launch > 0 && (outcome < FTGCR_RESIDENT_LATE || outcome > FTGCR_RESIDENT_REFUSED)))
+        return fail(h, FTGCR_E_INVALID, "launch or outcome out of range");
+    h->test_launch = launch;
+    h->test_outcome = outcome;
     return FTGCR_OK;
 }
 

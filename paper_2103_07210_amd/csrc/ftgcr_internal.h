@@ -194,7 +194,7 @@ struct Inst {
     unsigned long long* xw;
     int nblk_res, rtx;
     // of a batch's launch (ResidentArgs::s_stop < 0): this member's
-    int res_new_norms;
+    int res_new_norms, res_leave;
     long long res_stop;
 };
 
@@ -274,7 +274,7 @@ constexpr size_t RES_WORDS = 2 * (size_t)RES_COPIES * NV_MAX * RES_BLOCKS * 2;
 // SolveState::res_fail: a launch whose blocks did not all start in time has
 // changed nothing but its exchange words; one that came apart later has
 // broken the solve (gather_status then reports BROKEN for its status)
-enum { RES_LATE = 1, RES_BROKEN = 2 };
+enum { RES_LATE = FTGCR_RESIDENT_LATE, RES_BROKEN = FTGCR_RESIDENT_BROKEN };
 constexpr int BROKEN = -2;
 
 // Wavefronts per block with which the resident kernel takes a problem of
@@ -288,10 +288,11 @@ template <typename T> bool resident_fits(int mesh, int H, int waves, int nblk, i
 // What a launch runs: steps until every instance has left RUNNING or executed
 // s_stop of them.
 struct ResidentArgs {
-    long long s_stop;  // < 0: each instance's own (Inst::res_stop, res_new_norms)
+    long long s_stop;  // < 0: each instance's own (Inst::res_stop, res_new_norms, res_leave)
     int nvmax;         // k + 1: the most sums in a round
     int new_norms;     // 1: form the state's norms of r anew first
     int time_mask, time_stride;   // options.profile_kernels
+    int leave;         // RES_LATE, RES_BROKEN: all blocks leave so (ftgcr_debug_resident), 0: none
 };
 template <typename T>
 hipError_t resident_run(const Table<T>& tb, const int* blk0, int total_blocks, int mesh, int H, int waves,
@@ -326,8 +327,9 @@ template <typename T> struct Launch {
     // fault events (single instance)
     static void event_prep(const Table<T>& tb, int vec, hipStream_t s);
     static void event_copy(const Table<T>& tb, int grid, hipStream_t s);
+    // again: a flip already counted, taken out or put back
     static void event_inject(const Table<T>& tb, int grid, const long long* idx, const unsigned char* bits,
-                             long long count, long long start, int bit, hipStream_t s);
+                             long long count, long long start, int bit, bool again, hipStream_t s);
     static void beta_dots(const Table<T>& tb, int total_st_blocks, hipStream_t s);
     static void gather_status(const Table<T>& tb, long long* out, hipStream_t s);
     // parity entry points (FP64 only)

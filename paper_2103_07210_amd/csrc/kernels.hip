@@ -1625,7 +1625,7 @@ __global__ void k_event_copy(Table<T> tb)
 
 template <typename T>
 __global__ void k_event_inject(Table<T> tb, const long long* idx, const unsigned char* bits, long long count,
-                               long long start, int bit0)
+                               long long start, int bit0, int again)
 {
     const Inst<T>& in = tb.inst[0];
     SolveState* st = in.st;
@@ -1641,7 +1641,7 @@ __global__ void k_event_inject(Table<T> tb, const long long* idx, const unsigned
         else if (vec == FTGCR_V_AP) write_xor<T>(in.AP[st->slot[st->nu]] + at, bit);
         else write_xor<T>(in.U[st->uslot[st->nu + 1]] + at, bit);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (!again && blockIdx.x == 0 && threadIdx.x == 0) {
         st->events_applied += 1;
         st->events_since_rb = 1;
         if (vec == FTGCR_V_P && st->ev_copy == 2)   // the basis holds p^nu itself now
@@ -1941,9 +1941,9 @@ void Launch<T>::event_copy(const Table<T>& tb, int grid, hipStream_t s)
 
 template <typename T>
 void Launch<T>::event_inject(const Table<T>& tb, int grid, const long long* idx, const unsigned char* bits,
-                             long long count, long long start, int bit, hipStream_t s)
+                             long long count, long long start, int bit, bool again, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_event_inject<T>, dim3(grid), dim3(256), 0, s, tb, idx, bits, count, start, bit);
+    hipLaunchKernelGGL(k_event_inject<T>, dim3(grid), dim3(256), 0, s, tb, idx, bits, count, start, bit, again ? 1 : 0);
 }
 
 template <typename T>

@@ -411,6 +411,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         if (lane == 0) s_wp[q][w] = v;
     };
 
+    const int leave = arg.s_stop < 0 ? in.res_leave : arg.leave;
     // The first exchange, before anything is written.  The detector compares
     // norms of r summed in one order: where these two (of r and of the backup's)
     // come from the streaming kernels, they are formed anew here.
@@ -433,6 +434,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
             partial(0, 0.0);
         }
         publish(norms ? 2 : 1);
+        if (leave == RES_LATE) return gave_up(RES_LATE);
         if (!collect(norms ? 2 : 1)) return gave_up(RES_LATE);
         if (tid == 0) {
             if (norms) {
@@ -812,6 +814,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         timed(2, step);
         __syncthreads();
     }
+    if (leave == RES_BROKEN) return gave_up(RES_BROKEN);
     // r back to its buffer, the state to memory (one block's copy: all agree)
     if (stores) {
         T* const rp = uniform(s_R[s_st.r_cur]);

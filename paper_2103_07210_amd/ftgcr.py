@@ -24,6 +24,7 @@ CONVERGED, MAX_STEPS, STAGNATED, BREAKDOWN = 0, 1, 2, 3
 METHOD_GCR, METHOD_GMRES = 0, 1
 MESH_LATLON, MESH_OCTAHEDRAL = 0, 1
 ORDER_AUTO, ORDER_X, ORDER_Z, ORDER_XCD = 0, 1, 2, 3
+RESIDENT_LATE, RESIDENT_BROKEN, RESIDENT_REFUSED = 1, 2, 3
 KMAX = 16
 LOG_CAP = 256
 NOALLOC_SCRATCH_BYTES = 64 << 20
@@ -32,7 +33,8 @@ EXPORTED = ["ftgcr_default_options", "ftgcr_create", "ftgcr_set_options", "ftgcr
             "ftgcr_set_stream", "ftgcr_workspace_bytes", "ftgcr_set_workspace", "ftgcr_solve",
             "ftgcr_solve_batch", "ftgcr_destroy", "ftgcr_last_error", "ftgcr_debug_apply_A",
             "ftgcr_debug_apply_Pinv", "ftgcr_kernel_times", "ftgcr_reset_kernel_times", "ftgcr_autotune",
-            "ftgcr_autotune_batch", "ftgcr_bw_probe", "ftgcr_solve_noalloc", "ftgcr_get_tiling"]
+            "ftgcr_autotune_batch", "ftgcr_bw_probe", "ftgcr_solve_noalloc", "ftgcr_get_tiling",
+            "ftgcr_debug_resident"]
 
 
 class FtgcrError(RuntimeError):
@@ -139,6 +141,8 @@ def load():
     lib.ftgcr_debug_apply_A.restype = ctypes.c_int
     lib.ftgcr_debug_apply_Pinv.argtypes = [H, vp, vp]
     lib.ftgcr_debug_apply_Pinv.restype = ctypes.c_int
+    lib.ftgcr_debug_resident.argtypes = [H, ctypes.c_int32, ctypes.c_int32]
+    lib.ftgcr_debug_resident.restype = ctypes.c_int
     lib.ftgcr_kernel_times.argtypes = [H, ctypes.POINTER(KernelTime), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
     lib.ftgcr_kernel_times.restype = ctypes.c_int
     lib.ftgcr_reset_kernel_times.argtypes = [H]
@@ -323,6 +327,11 @@ class Solver:
         _check(load().ftgcr_debug_apply_Pinv(self._h, ctypes.c_void_p(r_t.data_ptr()),
                                              ctypes.c_void_p(e.data_ptr())), self._h)
         return e
+
+    def debug_resident(self, launch: int, outcome: int = RESIDENT_LATE):
+        """Test entry: how launches of many steps end from the given one on
+        (RESIDENT_*; launch 0: normally)."""
+        _check(load().ftgcr_debug_resident(self._h, launch, outcome), self._h)
 
     def autotune(self, rhs, k: int = 3, steps: int = 24) -> int:
         """Time `steps` steps per stencil tiling on this problem and keep the
