@@ -658,8 +658,6 @@ struct DevEvent {
     const unsigned char* bits;   // device or null
 };
 
-// Steps a resident launch runs at most before the host looks at the state.
-constexpr long long RES_STEPS = 4096;
 // Rounds of launches a batch takes without progress (5 s each at most)
 constexpr int RES_LATE_MAX = 12;
 

@@ -271,6 +271,10 @@ constexpr int RES_BLOCKS = 256;
 // tagged words a value
 constexpr int RES_COPIES = 4;
 constexpr size_t RES_WORDS = 2 * (size_t)RES_COPIES * NV_MAX * RES_BLOCKS * 2;
+// Steps a launch runs at most before the host looks at the state, and more
+// rounds than it exchanges (three a step and the first)
+constexpr long long RES_STEPS = 4096;
+constexpr unsigned RES_ROUNDS = 3 * RES_STEPS + 4;
 // SolveState::res_fail: a launch whose blocks did not all start in time has
 // changed nothing but its exchange words; one that came apart later has
 // broken the solve (gather_status then reports BROKEN for its status)

@@ -430,6 +430,8 @@ __global__ void k_init_state(Table<T> tb, int k, int ft, int mixed, long long ma
     const int m = blockIdx.x;
     if (m >= tb.n || threadIdx.x != 0) return;
     SolveState* st = tb.inst[m].st;
+    // a launch that failed has left words of rounds the state does not count
+    if (st->res_fail) st->res_seq += RES_ROUNDS;
     st->res_fail = 0;
     if (reset_counters) {
         st->s = 0;

@@ -70,3 +70,46 @@ def test_flip_in_r_before_a_launch_that_does_not_run(ft, oracle_mod, pb, which, 
     assert st["detections"] == 1
     _same_as_oracle(ft, _oracle(oracle_mod, pb), rhs, x, st, 3, plan)
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("pb", [Problem(64, 32, 8), OctProblem(12, 21)], ids=lambda v: str(v.shape))
+def test_solve_after_a_failed_one(ft, pb, precision):
+    """A launch that came apart after 40 steps fails its solve; the rounds it
+    exchanged leave no trace in the handle's next solves (a handle without a
+    past gives the same bits)."""
+    print("[gpu-case] after a failed solve", pb, precision, flush=True)
+    s, fresh = ft.Solver(pb, precision, kmax=3), ft.Solver(pb, precision, kmax=3)
+    s.debug_resident(1, ft.RESIDENT_BROKEN)
+    s.set_options(max_steps=40)
+    with pytest.raises(ft.FtgcrError) as e:
+        s.solve(I.rhs(pb, 32), tol=1e-10, k=3)
+    assert e.value.code == ft.E_HIP
+    s.debug_resident(0)
+    s.set_options(max_steps=100000)
+    for seed in (33, 34):
+        x, st = s.solve(I.rhs(pb, seed), tol=1e-8, k=3)
+        y, su = fresh.solve(I.rhs(pb, seed), tol=1e-8, k=3)
+        assert st["status"] == ft.CONVERGED and st["steps_executed"] == su["steps_executed"]
+        assert bool((x == y).all())
+    s.close()
+    fresh.close()
+
+
+def test_batch_after_a_failed_one(ft):
+    print("[gpu-case] after a failed batch", flush=True)
+    pbs = [Problem(64, 32, 8), Problem(40, 20, 15), Problem(64, 32, 7)]
+    groups = [[ft.Solver(pb, kmax=3) for pb in pbs] for _ in range(2)]
+    rhs = [I.rhs(pb, 35 + m) for m, pb in enumerate(pbs)]
+    groups[0][2].debug_resident(1, ft.RESIDENT_BROKEN)
+    with pytest.raises(ft.FtgcrError) as e:
+        ft.solve_batch(groups[0], rhs, tols=[1e-8] * 3, k=3)
+    assert e.value.code == ft.E_HIP
+    groups[0][2].debug_resident(0)
+    out = [ft.solve_batch(g, rhs, tols=[1e-8] * 3, k=3) for g in groups]
+    for x, y, a, b in zip(out[0][0], out[1][0], out[0][1], out[1][1]):
+        assert a["status"] == ft.CONVERGED and a["steps_executed"] == b["steps_executed"]
+        assert bool((x == y).all())
+    for g in groups:
+        for s in g:
+            s.close()
