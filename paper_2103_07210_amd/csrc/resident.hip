@@ -824,15 +824,16 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
     if (lb == 0) {
         __syncthreads();
         if (tid == 0) {
-            s_st.res_seq = seq;
-            s_st.res_fail = __hip_atomic_load(as_global(&gst->res_fail), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            as_global_mut(gst)->res_seq = seq;
             for (int q = 0; q < 3; ++q) {
                 s_st.res_ticks[q] = ticks[q];
                 s_st.res_counts[q] = counts[q];
             }
         }
         __syncthreads();
-        for (int q = tid; q < ST_WORDS; q += nthr)
+        // (not the first word: another block may still set res_fail there)
+        static_assert(offsetof(SolveState, res_ticks) == 8, "res_fail and res_seq are the first word");
+        for (int q = tid + 1; q < ST_WORDS; q += nthr)
             as_global_mut(reinterpret_cast<long long*>(gst))[q] = s_words[q];
     }
 }
