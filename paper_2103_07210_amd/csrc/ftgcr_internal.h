@@ -69,7 +69,8 @@ struct SolveState {
     int res_fail;        // RES_LATE, RES_BROKEN: a resident kernel's block waited in vain
     unsigned res_seq;    // rounds of exchanges the resident kernels of this handle have run
     unsigned long long res_ticks[3];   // the last resident launch's timed rounds (100 MHz)
-    int res_counts[3], res_pad;
+    int res_counts[3];
+    unsigned res_gate;   // the last resident launch's verdict: its first round's number, doubled, + 1 if it went on
     int status;          // RUNNING or an FTGCR_* outcome
     int active;          // 1: this step goes on to P^{-1}, L and the new direction
     int nu;              // pass index of the current step
@@ -272,7 +273,7 @@ constexpr int RES_BLOCKS = 256;
 constexpr int RES_COPIES = 4;
 constexpr size_t RES_WORDS = 2 * (size_t)RES_COPIES * NV_MAX * RES_BLOCKS * 2;
 // Steps a launch runs at most before the host looks at the state, and more
-// rounds than it exchanges (three a step and the first)
+// rounds than it exchanges (three a step and two before them)
 constexpr long long RES_STEPS = 4096;
 constexpr unsigned RES_ROUNDS = 3 * RES_STEPS + 4;
 // SolveState::res_fail: a launch whose blocks did not all start in time has

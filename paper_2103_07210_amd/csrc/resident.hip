@@ -36,10 +36,11 @@
 //
 // All blocks of a launch have to run at once: the launch is cooperative, one
 // block per CU at most, and every wait is bounded (a wait that ends in vain
-// sets SolveState::res_fail and the block leaves).  The first exchange comes
-// before any vector is written: where another stream's work keeps blocks from
-// starting that long, the launch ends with the solve as it was (RES_LATE) and
-// the host goes on in the streaming kernels (a batch: launches again).
+// sets SolveState::res_fail and the block leaves).  Before anything else all
+// blocks come to one verdict on whether they are all there: where another
+// stream's work keeps blocks from starting that long, the launch ends with the
+// solve as it was (RES_LATE) and the host goes on in the streaming kernels (a
+// batch: launches again).
 #include <algorithm>
 
 #include "device.h"
@@ -106,6 +107,59 @@ __device__ __forceinline__ void far_store(T* base, unsigned at, T v)
     __hip_atomic_store(elem_mut(base, at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Where a block's words of a round lie: [parity][copy][value][block][half].
+__device__ __forceinline__ size_t word_at(unsigned seq, int copy, int value, int block)
+{
+    return ((((size_t)(seq & 1) * RES_COPIES + copy) * NV_MAX + value) * RES_BLOCKS + block) * 2;
+}
+
+// Whether all blocks of the launch run: an exchange of round `seq` without
+// values, and one verdict on it for all blocks, which the first block that knows
+// sets (one that has seen every block for it, one that has waited in vain
+// against).  Every thread of the block calls it; -1: the verdict was for it, but
+// the words did not come.  (Out of line: inlined it moves the step loop's
+// registers about, 256 x 128 x 32 22.5 -> 22.9 us a step.)
+__device__ __noinline__ int all_there(u64* xw, unsigned* gate, unsigned seq, int lb, int nblk, bool none, int* sh)
+{
+    const int tid = threadIdx.x;
+    if (tid < RES_COPIES) word_store(xw + word_at(seq, tid, 0, lb), (u64)seq << 32);
+    for (int turn = 0;; ++turn) {
+        if (tid == 0) sh[0] = none ? 0 : 1;
+        __syncthreads();
+        if (!none) {
+            u64 began = 0;
+            for (int b = tid; b < nblk; b += blockDim.x) {
+                const u64* p = xw + word_at(seq, lb & (RES_COPIES - 1), 0, b);
+                for (int spin = 0; (unsigned)(word_load(p) >> 32) != seq; ++spin) {
+                    if ((spin & 255) != 255) continue;
+                    const u64 now = wall_clock64();
+                    if (began == 0) began = now;
+                    if (now - began > WAIT_TICKS) {
+                        sh[0] = 0;
+                        break;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        const int all = sh[0];
+        if (tid == 0) {
+            const unsigned mine = (seq << 1) | (unsigned)all;
+            unsigned u = __hip_atomic_load(as_global(gate), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while ((u >> 1) != (mine >> 1)) {
+                const unsigned v = atomicCAS(gate, u, mine);
+                u = v == u ? mine : v;
+            }
+            sh[1] = (int)(u & 1);
+        }
+        __syncthreads();
+        if (!sh[1]) return 0;
+        if (all) return 1;
+        if (turn > 0) return -1;   // (another block has read them all: the second time they are there)
+        __syncthreads();
+    }
+}
+
 // Nothing moves across: without it the scheduler starts the loads of all
 // rows at once and spills what they return.
 __device__ __forceinline__ void fence_rows()
@@ -149,7 +203,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
     __shared__ T* s_AP[KMAX + 1];
     __shared__ T* s_ap[KMAX + 1];   // this step's L(p^l) and basis
     __shared__ T* s_u[KMAX + 2];
-    __shared__ int s_fail;
+    __shared__ int s_fail, s_there[2];
     // the blocks' partials of up to arg.nvmax sums, e of the tile, the pivots where
     // registers are short, then L(p^l) of the first `ncache` l (read twice a
     // step)
@@ -165,6 +219,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
     const int nblk = in.nblk_res;
     const int lgb = 32 - __builtin_clz(nblk - 1 > 0 ? nblk - 1 : 1);   // blocks of a value: 1 << lgb slots
     u64* const xw = (u64*)in.xw;
+    const int leave = arg.s_stop < 0 ? in.res_leave : arg.leave;
     const Geo& g = in.g;
     const int nx = g.nx, ny = g.ny, nz = g.nz, ncols = g.ncols;
     const CT opsig = (CT)g.opsig;
@@ -197,6 +252,16 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
     T* const s_cache = s_e + nw * H * 64 * (INV_LDS ? 2 : 1) + w * H * 64 + lane;   // [l][wavefront][row][lane]
     const int cache_step = nw * H * 64;
     __syncthreads();
+
+    unsigned seq = s_st.res_seq;
+    if (s_st.status == RUNNING) {   // before anything is written
+        seq += 1;
+        const int there = all_there(xw, &gst->res_gate, seq, lb, nblk, leave == RES_LATE, s_there);
+        if (there <= 0) {
+            if (tid == 0) atomicMax(&gst->res_fail, there < 0 ? RES_BROKEN : RES_LATE);
+            return;
+        }
+    }
 
     // this lane's column and its half
     const int upper = lane >> 5;
@@ -283,7 +348,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         meet_den = mm + mw * zx;
     }
 
-    unsigned seq = s_st.res_seq;
+    fence_rows();
     T r[H], ap[H];
     auto load_state = [&]() {   // r and L(p^nu) as the state names them
         const T* rp = uniform(s_R[s_st.r_cur]);
@@ -326,14 +391,13 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
             double v = 0.0;
             for (int z = 0; z < nw; ++z) v += s_wp[q][z];
             const u64 b = (u64)__double_as_longlong(v), tag = (u64)seq << 32;
-            u64* p = xw + (((size_t)(seq & 1) * RES_COPIES + copy) * NV_MAX * RES_BLOCKS + q * RES_BLOCKS + lb) * 2;
+            u64* p = xw + word_at(seq, copy, q, lb);
             word_store(p, tag | (b & 0xffffffffull));
             word_store(p + 1, tag | (b >> 32));
         }
     };
     auto collect = [&](int nv) -> bool {
-        const u64* base =
-            xw + ((size_t)(seq & 1) * RES_COPIES + (lb & (RES_COPIES - 1))) * NV_MAX * RES_BLOCKS * 2;
+        const u64* base = xw + word_at(seq, lb & (RES_COPIES - 1), 0, 0);
         const int items = nv << lgb, mask = (1 << lgb) - 1;
         constexpr int G = 4;
         int first = tid;
@@ -388,8 +452,8 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         __syncthreads();
         return true;
     };
-    auto gave_up = [&](int how) {   // (its result awaited: blocks that start later see it)
-        if (tid == 0 && atomicMax(&gst->res_fail, how) > RES_BROKEN) s_fail = 1;
+    auto gave_up = [&](int how) {
+        if (tid == 0) atomicMax(&gst->res_fail, how);
     };
     auto decide = [&](double rn, double rs) {   // thread 0, on this block's copy of the state
         decide_step(&s_st, log, rn, rs, hist, hist_cap);
@@ -411,41 +475,29 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
         if (lane == 0) s_wp[q][w] = v;
     };
 
-    const int leave = arg.s_stop < 0 ? in.res_leave : arg.leave;
-    // The first exchange, before anything is written.  The detector compares
-    // norms of r summed in one order: where these two (of r and of the backup's)
-    // come from the streaming kernels, they are formed anew here.
-    if (s_st.status == RUNNING) {
-        const bool norms = (arg.s_stop < 0 ? in.res_new_norms : arg.new_norms) != 0;
-        if (norms) {
-            const T* rp = uniform(s_R[s_st.r_bak]);
-            double a0 = 0.0, a1 = 0.0;
+    // The detector compares norms of r summed in one order: where these two (of
+    // r and of the backup's) come from the streaming kernels, they are formed
+    // anew here.
+    if (s_st.status == RUNNING && (arg.s_stop < 0 ? in.res_new_norms : arg.new_norms) != 0) {
+        const T* rp = uniform(s_R[s_st.r_bak]);
+        double a0 = 0.0, a1 = 0.0;
 #pragma unroll
-            for (int q = 0; q < H; ++q) {
-                a0 = fma((double)r[q], (double)r[q], a0);
-                const double b = q >= H - nmine ? (double)far_load(rp, at[q]) : 0.0;
-                a1 = fma(b, b, a1);
-                settle(a0);
-                settle(a1);
-            }
-            partial(0, a0);
-            partial(1, a1);
-        } else {
-            partial(0, 0.0);
+        for (int q = 0; q < H; ++q) {
+            a0 = fma((double)r[q], (double)r[q], a0);
+            const double b = q >= H - nmine ? (double)far_load(rp, at[q]) : 0.0;
+            a1 = fma(b, b, a1);
+            settle(a0);
+            settle(a1);
         }
-        publish(norms ? 2 : 1);
-        if (leave == RES_LATE) return gave_up(RES_LATE);
-        if (!collect(norms ? 2 : 1)) return gave_up(RES_LATE);
+        partial(0, a0);
+        partial(1, a1);
+        publish(2);
+        if (!collect(2)) return gave_up(RES_BROKEN);
         if (tid == 0) {
-            if (norms) {
-                s_st.rr_old = s_sum[0];
-                s_st.b_rr = s_sum[1];
-            }
-            // blocks that gave up before this one started left their words behind
-            if (__hip_atomic_load(as_global(&gst->res_fail), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) s_fail = 1;
+            s_st.rr_old = s_sum[0];
+            s_st.b_rr = s_sum[1];
         }
         __syncthreads();
-        if (s_fail) return;
     }
 
     // kernel timing (options.profile_kernels): the three rounds' durations on

@@ -113,3 +113,29 @@ def test_batch_after_a_failed_one(ft):
     for g in groups:
         for s in g:
             s.close()
+
+
+@pytest.mark.parametrize("outcome", ["LATE", "REFUSED"])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("pb", [Problem(250, 33, 9), OctProblem(12, 21)], ids=lambda v: str(v.shape))
+def test_no_launch_runs(ft, pb, precision, outcome):
+    """From the first launch on: the streaming kernels' result to the last bit;
+    blocks that start late in the next solve's launches are counted afresh."""
+    print("[gpu-case] no launch runs", pb, precision, outcome, flush=True)
+    rhs = I.rhs(pb, 36)
+    order = ft.ORDER_XCD if isinstance(pb, OctProblem) else ft.ORDER_X   # the mesh's default
+    s, streaming = ft.Solver(pb, precision, kmax=3), ft.Solver(pb, precision, kmax=3, order_stencil=order)
+    fresh = ft.Solver(pb, precision, kmax=3)
+    s.debug_resident(1, getattr(ft, "RESIDENT_" + outcome))
+    x, st = s.solve(rhs, tol=1e-8, k=3)
+    y, su = streaming.solve(rhs, tol=1e-8, k=3)
+    assert st["status"] == ft.CONVERGED and st["steps_executed"] == su["steps_executed"]
+    assert bool((x == y).all())
+    if outcome == "LATE":
+        s.debug_resident(0)
+        x, st = s.solve(rhs, tol=1e-8, k=3)
+        y, su = fresh.solve(rhs, tol=1e-8, k=3)
+        assert st["steps_executed"] == su["steps_executed"]
+        assert bool((x == y).all())
+    for h in (s, streaming, fresh):
+        h.close()
