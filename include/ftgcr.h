@@ -424,7 +424,8 @@ ftgcr_status ftgcr_debug_apply_Pinv(ftgcr_handle* h, const double* in_dev, doubl
  *            E_HIP, a later one on the handle starts afresh);
  *   REFUSED  the device did not take the launch (as LATE).
  * All blocks leave by the same exits as in those cases.  In a batch BROKEN and
- * LATE hold for the member with this handle, REFUSED for the whole launch.
+ * LATE hold for the member with this handle, REFUSED for the whole launch, and
+ * after LATE and REFUSED all its members go on in the streaming kernels.
  * E_INVALID for other arguments. */
 enum { FTGCR_RESIDENT_LATE = 1, FTGCR_RESIDENT_BROKEN = 2, FTGCR_RESIDENT_REFUSED = 3 };
 ftgcr_status ftgcr_debug_resident(ftgcr_handle* h, int32_t launch, int32_t outcome);

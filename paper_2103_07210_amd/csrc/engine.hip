@@ -658,8 +658,6 @@ struct DevEvent {
     const unsigned char* bits;   // device or null
 };
 
-// Rounds of launches a batch takes without progress (5 s each at most)
-constexpr int RES_LATE_MAX = 12;
 
 const char* const kKernelNames[3] = {"update_thomas", "stencil_dots", "dir_update"};
 
@@ -1477,44 +1475,57 @@ bool plan_resident_batch(ftgcr_handle* const* hs, int n, int k, ResidentBatch& r
 
 // The steps of a batch planned by plan_resident_batch, from every member's
 // start to its outcome.  Members with fault events ahead run first, each to
-// the step before its next one; once none is left, all run to their end.
+// the step before its next one; once none is left, all run to their end.  When
+// a launch does not run (its blocks do not start together, or the device does
+// not take it), the members still running are left to the streaming kernels:
+// `left`, with the steps each has executed in `base` and its next event in
+// `evp`.
 // inst, blk0, status: device tables with room for n members; single(m) the
 // member's own launch table, apply(m, event) injects an event.
 template <class Single, class Apply>
 ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const ResidentBatch& rb,
                                 const std::vector<Inst<double>>& ins, const std::vector<std::vector<DevEvent>>& evs,
                                 const Table<double>& tb_all, long long* status, Inst<double>* inst, int* blk0,
+                                std::vector<int>& left, std::vector<long long>& base, std::vector<size_t>& evp,
                                 Single&& single, Apply&& apply)
 {
     using L = Launch<double>;
     ftgcr_handle* h0 = hs[0];
     hipStream_t s = h0->stream;
     const int most = std::min(h0->cus, RES_BLOCKS);
-    std::vector<size_t> evp(n, 0);
     std::vector<char> resident_norms(n, 0);   // the member's state holds the resident kernel's norms
     std::vector<long long> host(2 * n), before(n, -1);
     std::vector<char> launched(n, 0), norms_before(n, 0);
-    int late = 0;   // rounds of launches in which a member's blocks did not start together
+    std::vector<std::vector<const DevEvent*>> on_r(n);   // events on r before the member's launch
     while (true) {
         L::gather_status(tb_all, status, s);
         HIP_TRY(h0, hipMemcpyAsync(host.data(), status, 2 * n * sizeof(long long), hipMemcpyDeviceToHost, s));
         HIP_TRY(h0, hipStreamSynchronize(s));
-        bool any = false, ahead = false, again = false;
+        bool any = false, ahead = false, stream_on = false;
         for (int m = 0; m < n; ++m) {
             if (host[2 * m] == BROKEN) return fail(h0, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
             if (host[2 * m] != RUNNING) continue;
             any = true;
             if (launched[m] && host[2 * m + 1] <= before[m]) {   // nothing of it has changed
                 resident_norms[m] = norms_before[m];
-                again = true;
+                stream_on = true;
+            } else {
+                on_r[m].clear();
             }
             while (evp[m] < evs[m].size() && evs[m][evp[m]].step <= host[2 * m + 1]) ++evp[m];
             ahead = ahead || evp[m] < evs[m].size();
         }
         if (!any) return FTGCR_OK;
-        if (again) {
-            if (++late > RES_LATE_MAX) return fail(h0, FTGCR_E_HIP, "the resident kernel's blocks did not run together");
+        if (stream_on) {
             L::resident_late(tb_all, s);
+            for (int m = 0; m < n; ++m) {
+                if (host[2 * m] != RUNNING) continue;
+                if (resident_norms[m])
+                    streaming_norms<double>(single(m), on_r[m], ins[m].nblk_col, hs[m]->H, s);
+                left.push_back(m);
+                base[m] = host[2 * m + 1];
+            }
+            return FTGCR_OK;
         }
         std::fill(launched.begin(), launched.end(), 0);
         std::vector<Inst<double>> act;
@@ -1556,7 +1567,10 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
                         streamed = true;
                         continue;
                     }
-                    for (; evp[m] < end; ++evp[m]) apply(m, evs[m][evp[m]]);
+                    for (; evp[m] < end; ++evp[m]) {
+                        if (evs[m][evp[m]].vec == FTGCR_V_R) on_r[m].push_back(&evs[m][evp[m]]);
+                        apply(m, evs[m][evp[m]]);
+                    }
                 }
                 Inst<double> in = ins[m];
                 in.rtx = rb.rtx[m];
@@ -1602,8 +1616,13 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
             Table<double> t{};
             t.inst = inst + go.at;
             t.n = go.count;
-            HIP_TRY(h0, resident_run<double>(t, blk0 + go.first, go.blocks, h0->geo.mesh, go.d->H, go.d->waves,
-                                             ResidentArgs{-1, k + 1, 0, 0, 0, 0}, s));
+            bool refused = false;
+            for (int q = go.at; q < go.at + go.count; ++q) refused = refused || act[q].res_leave == FTGCR_RESIDENT_REFUSED;
+            if (refused || resident_run<double>(t, blk0 + go.first, go.blocks, h0->geo.mesh, go.d->H, go.d->waves,
+                                                ResidentArgs{-1, k + 1, 0, 0, 0, 0}, s) != hipSuccess) {
+                (void)hipGetLastError();
+                break;   // its members are found unchanged
+            }
         }
         HIP_TRY(h0, hipStreamSynchronize(s));   // act and pre are read until here
     }
@@ -1725,10 +1744,16 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
         return FTGCR_OK;
     };
     ResidentBatch rb;
+    std::vector<long long> base(n, 0);   // a member's steps before `launched` counts
     if (plan_resident_batch(hs, n, k, rb)) {
-        rc = run_resident_batch(hs, n, k, rb, ins, evs, tb_all, B.status, B.inst, B.blk0, single, apply);
-        if (rc != FTGCR_OK) return rc;
         members.clear();
+        rc = run_resident_batch(hs, n, k, rb, ins, evs, tb_all, B.status, B.inst, B.blk0, members, base, evp, single,
+                                apply);
+        if (rc != FTGCR_OK) return rc;
+        if (!members.empty()) {
+            rc = upload_batch(h0, ins, members, H, B.inst, B.blk0, sh, tb);
+            if (rc != FTGCR_OK) return rc;
+        }
     }
     while (!members.empty()) {
         // fault events of the next step, member by member: x, r, p, L(p)
@@ -1737,8 +1762,9 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
         bool any_event = false;
         std::vector<std::pair<int, const DevEvent*>> mid;
         for (int m : members) {
-            while (evp[m] < evs[m].size() && evs[m][evp[m]].step <= launched) ++evp[m];
-            while (evp[m] < evs[m].size() && evs[m][evp[m]].step == launched + 1) {
+            const long long at = base[m] + launched;
+            while (evp[m] < evs[m].size() && evs[m][evp[m]].step <= at) ++evp[m];
+            while (evp[m] < evs[m].size() && evs[m][evp[m]].step == at + 1) {
                 const DevEvent& ev = evs[m][evp[m]++];
                 if (ev.vec == FTGCR_V_E) mid.push_back({m, &ev});
                 else apply(m, ev);
@@ -1747,7 +1773,8 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
         }
         long long cnt = any_event ? 1 : chunk;
         for (int m : members)
-            if (evp[m] < evs[m].size()) cnt = std::min<long long>(cnt, std::max<long long>(1, evs[m][evp[m]].step - 1 - launched));
+            if (evp[m] < evs[m].size())
+                cnt = std::min<long long>(cnt, std::max<long long>(1, evs[m][evp[m]].step - 1 - base[m] - launched));
         if (cnt == chunk && !any_event && h0->opt.use_graphs) {
             rc = replay();
             if (rc != FTGCR_OK) return rc;

@@ -39,8 +39,7 @@
 // sets SolveState::res_fail and the block leaves).  Before anything else all
 // blocks come to one verdict on whether they are all there: where another
 // stream's work keeps blocks from starting that long, the launch ends with the
-// solve as it was (RES_LATE) and the host goes on in the streaming kernels (a
-// batch: launches again).
+// solve as it was (RES_LATE) and the host goes on in the streaming kernels.
 #include <algorithm>
 
 #include "device.h"

@@ -139,3 +139,29 @@ def test_no_launch_runs(ft, pb, precision, outcome):
         assert bool((x == y).all())
     for h in (s, streaming, fresh):
         h.close()
+
+
+@pytest.mark.parametrize("outcome", ["LATE", "REFUSED"])
+@pytest.mark.parametrize("launch", [1, 2, 4])
+@pytest.mark.parametrize("mesh", ["lat-lon", "octahedral"])
+def test_batch_goes_on_streaming(ft, oracle_mod, mesh, launch, outcome):
+    """One member's launches do not run from the given one on (the second starts
+    at the flips of its step 6): every member ends as alone, with the flips
+    before and after that."""
+    print("[gpu-case] batch goes on streaming", mesh, launch, outcome, flush=True)
+    pbs = ([Problem(64, 32, 8), Problem(40, 20, 17), Problem(33, 18, 8), Problem(64, 16, 16)] if mesh == "lat-lon"
+           else [OctProblem(7, 21), OctProblem(9, 17), OctProblem(5, 30)])
+    rhs = [I.rhs(pb, 40 + m) for m, pb in enumerate(pbs)]
+    n = [pb.n for pb in pbs]
+    plans = [[] for _ in pbs]
+    plans[0] = [FaultEvent(6, "r", 52, start=0, count=n[0]), FaultEvent(6, "x", 40, start=0, count=n[0]),
+                FaultEvent(31, "r", 62, idx=np.array([n[0] // 2])), FaultEvent(33, "e", 62, idx=np.array([3])),
+                FaultEvent(60, "ap", 62, idx=np.array([n[0] - 1]))]
+    plans[2] = [FaultEvent(9, "r", 52, start=0, count=n[2]), FaultEvent(47, "r", 62, idx=np.array([5]))]
+    solvers = [ft.Solver(pb, kmax=3) for pb in pbs]
+    solvers[0].debug_resident(launch, getattr(ft, "RESIDENT_" + outcome))
+    xs, sts = ft.solve_batch(solvers, rhs, tols=[1e-10] * len(pbs), k=3, plans=plans)
+    for m, pb in enumerate(pbs):
+        _same_as_oracle(ft, _oracle(oracle_mod, pb), rhs[m], xs[m], sts[m], 3, plans[m])
+    for s in solvers:
+        s.close()
