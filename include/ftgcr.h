@@ -133,7 +133,10 @@ typedef struct {
                                 the first member: stencil levels per block of
                                 the combined launches (1, 2, 4, 8 or 16; 0 =
                                 the largest member's own tiling); set by
-                                ftgcr_autotune_batch                            */
+                                ftgcr_autotune_batch, whose choice leaves
+                                batches that fit the GPU's registers their
+                                cooperative launches; any other value rules
+                                those out, as levels_per_block does            */
     int32_t method;          /* Krylov method of ftgcr_solve: FTGCR_METHOD_GCR
                                 (FT-GCR(k), Algorithm 1) or FTGCR_METHOD_GMRES
                                 (the same fault layer on restarted GMRES(k);

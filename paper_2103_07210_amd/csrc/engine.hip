@@ -99,6 +99,7 @@ struct ftgcr_handle {
     // ftgcr_autotune's choice of them (-1: none)
     int ord_st = ORD_X, ord_dir = ORD_X;
     int tuned_ord_st = -1, tuned_ord_dir = -1;
+    int tuned_batch_kc = 0;   // options.batch_levels_per_block as ftgcr_autotune_batch left it
 
     // kernel timing (options.profile_kernels)
     struct Pending {
@@ -1438,6 +1439,9 @@ struct ResidentBatch {
 // Whether every member of the batch runs there (else the batch streams).
 bool plan_resident_batch(ftgcr_handle* const* hs, int n, int k, ResidentBatch& rb)
 {
+    // a tiling asked for in the options means the streaming kernels
+    const int bkc = hs[0]->opt.batch_levels_per_block;
+    if (bkc != hs[0]->tuned_batch_kc && (bkc == 1 || bkc == 2 || bkc == 4 || bkc == 8 || bkc == 16)) return false;
     rb.rtx.assign(n, 0);
     rb.nblk.assign(n, 0);
     std::map<int, std::vector<int>> by_depth;
@@ -1964,6 +1968,7 @@ ftgcr_status ftgcr_set_options(ftgcr_handle* h, const ftgcr_options* opt)
         return fail(h, FTGCR_E_INVALID, "invalid options");
     if (opt->method == FTGCR_METHOD_GMRES && h->precision != FTGCR_FP64)
         return fail(h, FTGCR_E_UNSUPPORTED, "FT-GMRES is built for FP64 handles");
+    if (opt->batch_levels_per_block != h->tuned_batch_kc) h->tuned_batch_kc = 0;
     h->opt = *opt;
     set_tiling(h);
     if (h->graph) {
@@ -2271,7 +2276,7 @@ ftgcr_status ftgcr_autotune_batch(ftgcr_handle* const* hs, int32_t n, const doub
         }
     }
     restore();
-    hs[0]->opt.batch_levels_per_block = best;
+    hs[0]->opt.batch_levels_per_block = hs[0]->tuned_batch_kc = best;
     if (chosen) *chosen = best;
     return FTGCR_OK;
 }

@@ -1,0 +1,64 @@
+"""Which solves and batches run in the resident kernel: a launch of it forced to
+end as broken fails the solve, so a solve that succeeds did not make one."""
+import pytest
+
+from paper_2103_07210_amd import inputs as I
+from paper_2103_07210_amd.inputs import Problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ft():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    from paper_2103_07210_amd import ftgcr
+    ftgcr.load()
+    return ftgcr
+
+
+def _resident(ft, solvers, call):
+    for s in solvers:
+        s.debug_resident(1, ft.RESIDENT_BROKEN)
+    try:
+        call()
+        return False
+    except ft.FtgcrError as e:
+        assert e.code == ft.E_HIP
+        return True
+    finally:
+        for s in solvers:
+            s.debug_resident(0)
+
+
+def test_tilings_asked_for_stream(ft):
+    print("[gpu-case] tilings asked for", flush=True)
+    pbs = [Problem(64, 32, 8), Problem(33, 18, 8)]
+    rhs = [I.rhs(pb, 50 + m) for m, pb in enumerate(pbs)]
+    solvers = [ft.Solver(pb, kmax=3, max_steps=9) for pb in pbs]
+
+    def single():
+        return _resident(ft, solvers[:1], lambda: solvers[0].solve(rhs[0], tol=1e-10, k=3))
+
+    def batch():
+        return _resident(ft, solvers, lambda: ft.solve_batch(solvers, rhs, tols=[1e-10] * 2, k=3))
+
+    assert single() and batch()
+    solvers[0].set_options(levels_per_block=4)
+    assert not single() and not batch()
+    solvers[0].set_options(levels_per_block=0, batch_levels_per_block=4)
+    assert single() and not batch()
+    # the autotuner's choice is of the streaming kernels' tiling alone
+    kc = ft.autotune_batch(solvers, rhs, k=3, steps=6)
+    assert solvers[0].options()["batch_levels_per_block"] == kc
+    assert batch()
+    solvers[0].set_options(batch_levels_per_block=2 * kc)
+    assert not batch()
+    solvers[0].set_options(batch_levels_per_block=kc)   # asked for now
+    assert not batch()
+    solvers[0].set_options(batch_levels_per_block=0)
+    assert batch()
+    for s in solvers:
+        s.close()
