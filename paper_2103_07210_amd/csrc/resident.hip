@@ -989,10 +989,14 @@ bool resident_fits(int mesh, int H, int waves, int nblk, int k)
     if (!f) return false;
     int dev = 0, coop = 0, cus = 0, per = 0, nc = 0;
     const size_t lds = resident_lds(f, H, waves, (int)sizeof(T), k, &nc);
-    if (hipGetDevice(&dev) != hipSuccess ||
+    hipFuncAttributes fa;
+    // (the limit of a launch's dynamic LDS belongs to the function, not to a
+    // handle: all there is beside the kernel's own, whatever this one needs)
+    if (hipGetDevice(&dev) != hipSuccess || hipFuncGetAttributes(&fa, f) != hipSuccess ||
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(RES_LDS - fa.sharedSizeBytes)) !=
+            hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, waves * 64, lds) != hipSuccess) {
         (void)hipGetLastError();
         return false;

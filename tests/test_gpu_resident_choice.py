@@ -62,3 +62,23 @@ def test_tilings_asked_for_stream(ft):
     assert batch()
     for s in solvers:
         s.close()
+
+
+def test_handles_of_other_sizes_and_kmax(ft):
+    """Handles that share a kernel and need more or less LDS of it keep their
+    launches whatever handle came last."""
+    print("[gpu-case] handles of other kmax", flush=True)
+    pbs = [(Problem(64, 32, 8), 16), (Problem(512, 16, 8), 4), (Problem(40, 8, 8), 1)]
+    solvers = [ft.Solver(pb, kmax=k, max_steps=20) for pb, k in pbs]
+    rhs = [I.rhs(pb, 52) for pb, _ in pbs]
+    for order in ((0, 1, 2), (2, 1, 0)):
+        for m in order:
+            for k in {1, pbs[m][1]}:
+                assert _resident(ft, [solvers[m]], lambda: solvers[m].solve(rhs[m], tol=1e-30, k=k))
+                x, st = solvers[m].solve(rhs[m], tol=1e-30, k=k)
+                one = ft.Solver(pbs[m][0], kmax=pbs[m][1], max_steps=20)
+                y, _ = one.solve(rhs[m], tol=1e-30, k=k)
+                assert st["steps_executed"] == 20 and bool((x == y).all())
+                one.close()
+    for s in solvers:
+        s.close()
