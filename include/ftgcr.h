@@ -117,7 +117,8 @@ typedef struct {
     int64_t hist_cap;        /* entries of the per-step residual history kept   */
     int32_t use_graphs;      /* 1: replay captured step sequences (hipGraph)     */
     int32_t levels_per_block;/* stencil kernels: levels per block (0 = auto;
-                                grids that fit the GPU's registers then run
+                                grids that fit the GPU's registers, where it
+                                is the quicker form, then run
                                 many steps in one cooperative launch, which
                                 any explicit tiling or block order rules out) */
     int32_t profile_kernels; /* time step kernels with a HIP event pair each,

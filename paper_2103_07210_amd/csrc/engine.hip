@@ -86,6 +86,7 @@ struct ftgcr_handle {
     // the resident kernel's shape (res_waves 0: this grid does not take it) and
     // exchange words (device)
     int res_waves = 0, nblk_res = 0, rtx = 0;
+    double res_gain = 0.0;    // microseconds a step it gains, about
     int cus = 0;              // of the device
     bool no_resident = false; // a tuner is timing the streaming kernels
     unsigned long long* xw = nullptr;
@@ -324,9 +325,23 @@ Inst<T> make_inst(const ftgcr_handle* h, const double* rhs, double* x, void* ws)
     return in;
 }
 
+// About the microseconds a step of a single solve takes in the streaming
+// kernels, measured at k = 3 as resident_step_us: launches, and passes over
+// vectors that the cache holds (grids that the resident kernel takes).
+double streaming_step_us(const ftgcr_handle* h)
+{
+    const double m = 1e-6 * (double)h->geo.n;
+    if (h->precision == FTGCR_MIXED) return (h->H <= 32 ? 33.0 : 31.0) + 10.0 * m;
+    return h->geo.mesh == FTGCR_MESH_OCTAHEDRAL ? 27.0 + 20.0 * m : 28.0 + 18.0 * m;
+}
+
 // Decide whether solves of this handle run in the resident kernel, and give
-// it its exchange words.  A grid it does not take, or a device without
-// cooperative launches, leaves the handle to the streaming kernels.
+// it its exchange words.  A grid it does not take, a device without cooperative
+// launches, or a form of the kernel that takes longer than the streaming
+// kernels on this grid leaves the handle to those.  Such forms are the ones
+// that spill: us a step, streaming and resident, binary32 O_119 x 64 74, 90,
+// O_87 x 64 59, 77, O_87 x 33 44, 47 (but O_119 x 33 54, 52), 512 x 128 x 64 74,
+// 78, O_12 x 96 31, 33; FP64 O_87 x 17 40, 47 (but O_119 x 32 67, 59).
 ftgcr_status setup_resident(ftgcr_handle* h)
 {
     if (h->precond != FTGCR_PRECOND_COLUMN) return FTGCR_OK;
@@ -337,6 +352,8 @@ ftgcr_status setup_resident(ftgcr_handle* h)
     if (w == 0 || !(mixed ? resident_fits<float>(g.mesh, h->H, w, h->nblk_res, h->kmax)
                           : resident_fits<double>(g.mesh, h->H, w, h->nblk_res, h->kmax)))
         return FTGCR_OK;
+    h->res_gain = streaming_step_us(h) - resident_step_us(g.mesh, h->H, mixed ? 4 : 8, w);
+    if (h->res_gain <= 0.0) return FTGCR_OK;
     HIP_TRY(h, hipMalloc(&h->xw, RES_WORDS * sizeof(unsigned long long)));
     HIP_TRY(h, hipMemset(h->xw, 0, RES_WORDS * sizeof(unsigned long long)));
     h->res_waves = w;

@@ -288,6 +288,8 @@ constexpr int BROKEN = -2;
 int resident_waves(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int* rtx, int* nblk);
 // The same for a given number of wavefronts per block (false: it does not).
 bool resident_shape(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int waves, int* rtx, int* nblk);
+// About the microseconds a step takes there.
+double resident_step_us(int mesh, int H, int elem_bytes, int waves);
 // Whether the device can hold the kernel's blocks all at once.
 template <typename T> bool resident_fits(int mesh, int H, int waves, int nblk, int k);
 // What a launch runs: steps until every instance has left RUNNING or executed

@@ -918,6 +918,28 @@ int resident_waves(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int
     return 0;
 }
 
+// Measured at k = 3 (MI355X), a step by template depth (4, 8, 16, 24, 28, 32, 40,
+// 48) and wavefronts per block (1, 2, 4, 8).  It hardly depends on the grid: a
+// block runs its columns' rows in sequence whatever the number of blocks.  What
+// steps up between the columns of a row is registers: at eight wavefronts FP64
+// halves of 16 and binary32 ones of 24 rows and more spill (up to 300 vector
+// registers of 256), at four binary32 ones of 48.
+double resident_step_us(int mesh, int H, int elem_bytes, int waves)
+{
+    static const unsigned char us[2][2][4][8] = {   // mesh; FP64, binary32; wavefronts; depth
+        {{{11, 12, 15, 18, 20, 21}, {13, 14, 18, 21, 23, 25}, {14, 16, 22, 27, 30, 31}, {18, 22, 37}},
+         {{11, 12, 14, 17, 19, 20, 23, 28}, {13, 14, 17, 20, 22, 23, 28, 33}, {14, 15, 19, 24, 26, 28, 34, 42},
+          {16, 19, 25, 41, 60, 78}}},
+        {{{11, 12, 15, 19, 22, 24}, {13, 15, 19, 24, 26, 29}, {14, 17, 25, 29, 36, 41}, {19, 25, 50}},
+         {{12, 12, 15, 19, 21, 22, 27, 33}, {13, 14, 18, 22, 25, 26, 33, 40}, {14, 16, 19, 24, 28, 30, 38, 46},
+          {16, 19, 25, 50, 68, 84}}}};
+    const int depths[] = {4, 8, 16, 24, 28, 32, 40, 48};
+    int d = 0, w = 0;
+    while (d < 7 && depths[d] < H) ++d;
+    while (w < 3 && (1 << w) < waves) ++w;
+    return us[mesh == FTGCR_MESH_OCTAHEDRAL ? 1 : 0][elem_bytes == 4 ? 1 : 0][w][d];
+}
+
 namespace {
 
 template <typename T>

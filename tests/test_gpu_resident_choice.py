@@ -1,9 +1,10 @@
 """Which solves and batches run in the resident kernel: a launch of it forced to
 end as broken fails the solve, so a solve that succeeds did not make one."""
+import numpy as np
 import pytest
 
 from paper_2103_07210_amd import inputs as I
-from paper_2103_07210_amd.inputs import Problem
+from paper_2103_07210_amd.inputs import OctProblem, Problem
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +83,28 @@ def test_handles_of_other_sizes_and_kmax(ft):
                 one.close()
     for s in solvers:
         s.close()
+
+
+# either side of where a form of the kernel stops paying
+FORMS = [("fp64", OctProblem(87, 17), False), ("fp64", OctProblem(119, 20), True), ("fp64", Problem(250, 129, 17), True),
+         ("mixed", OctProblem(87, 33), False), ("mixed", OctProblem(119, 33), True), ("mixed", OctProblem(87, 57), False),
+         ("mixed", Problem(250, 129, 41), True), ("mixed", Problem(250, 129, 57), False),
+         ("mixed", OctProblem(12, 81), False), ("mixed", OctProblem(12, 80), True), ("mixed", Problem(64, 32, 96), True)]
+
+
+@pytest.mark.parametrize("precision,pb,resident", FORMS, ids=lambda v: str(getattr(v, "shape", v)))
+def test_forms_that_pay(ft, oracle_mod, precision, pb, resident):
+    """Whichever runs, the first steps are the oracle's (mixed: one round of 8
+    steps, vectors rounded to 2^-24, ten roundings a step and a growth of 100)."""
+    print("[gpu-case] forms", precision, pb, flush=True)
+    rhs = I.rhs(pb, 53)
+    opts = {} if precision == "fp64" else {"max_refinements": 1, "inner_max_steps": 8, "inner_tol": 1e-12}
+    s = ft.Solver(pb, precision, kmax=3, max_steps=8, **opts)
+    assert _resident(ft, [s], lambda: s.solve(rhs, tol=1e-14, k=3)) == resident
+    x, st = s.solve(rhs, tol=1e-14, k=3)
+    o = (oracle_mod.OctOracle if isinstance(pb, OctProblem) else oracle_mod.Oracle)(pb)
+    xo, _, _, _ = o.solve(rhs, tol=1e-14, k=3, max_steps=8)
+    assert st["steps_executed"] == 8
+    x, xo = x.cpu().numpy().ravel(), np.asarray(xo).ravel()
+    assert np.linalg.norm(x - xo) <= (1e-10 if precision == "fp64" else 1e-3) * np.linalg.norm(xo)
+    s.close()
