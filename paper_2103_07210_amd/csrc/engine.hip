@@ -858,6 +858,28 @@ struct Runner {
         return FTGCR_OK;
     }
 
+    // Whether a resident launch of the steps before event `next` pays: it loads
+    // the state and forms the columns' pivots, and where the event's step is not
+    // resident (e) the norms have to be formed anew on both sides.  (Before an
+    // event of another kind the next launch gains that step too.)
+    // Microseconds a step, streaming and resident, 64 x 32 x 8, 256 x 128 x 32
+    // and O_40 x 51, k = 3: flips in x every step 58, 58; 72, 80; 64, 84; every
+    // second 44, 34; 62, 52; 55, 56; every fourth 36, 22; 55, 38; 50, 42; flips
+    // in e every second 43, 50; 60, 70; 54, 73; every fourth 35, 31; 54, 47; 48,
+    // 51; every eighth 30, 21; 50, 36; 45, 39.
+    bool pays_until(const std::vector<DevEvent>& evs, size_t next, long long launched, bool event_now) const
+    {
+        const double entry = 12.0 + 1.2 * h->H;
+        bool leaves = false;
+        size_t after = next;   // the event after it
+        for (; after < evs.size() && evs[after].step == evs[next].step; ++after)
+            leaves = leaves || evs[after].vec == FTGCR_V_E;
+        const long long gap = evs[next].step - 1 - launched;
+        if (leaves) return (double)gap * h->res_gain > entry + 0.8 * h->H;
+        const bool stays = after == evs.size() || (double)(evs[after].step - evs[next].step) * h->res_gain > entry;
+        return (double)(gap + (stays && !event_now ? 1 : 0)) * h->res_gain > entry;
+    }
+
     // Enqueue steps until the device reports an outcome.  `launched` is the
     // number of steps executed so far (the device's s).
     ftgcr_status run_steps(int k, long long launched, long long cap, const std::vector<DevEvent>& evs)
@@ -884,6 +906,9 @@ struct Runner {
             while (evp < evs.size() && evs[evp].step <= launched) ++evp;
             const bool event_now = evp < evs.size() && evs[evp].step == launched + 1;
             bool resident = use_resident(h) && !late;
+            size_t next = evp;   // the first event of a later step
+            while (next < evs.size() && evs[next].step <= launched + 1) ++next;
+            if (resident && next < evs.size()) resident = pays_until(evs, next, launched, event_now);
             if (event_now && resident) {
                 // events at the start of a step come between two launches of
                 // the resident kernel; one inside a step (e), or one on r

@@ -108,3 +108,24 @@ def test_forms_that_pay(ft, oracle_mod, precision, pb, resident):
     x, xo = x.cpu().numpy().ravel(), np.asarray(xo).ravel()
     assert np.linalg.norm(x - xo) <= (1e-10 if precision == "fp64" else 1e-3) * np.linalg.norm(xo)
     s.close()
+
+
+@pytest.mark.parametrize("vec,every,resident", [("x", 1, False), ("x", 2, True), ("e", 2, False), ("e", 4, True)])
+def test_events_in_close_succession(ft, oracle_mod, vec, every, resident):
+    """Launches between events where they pay; the same solve either way."""
+    print("[gpu-case] events", vec, every, flush=True)
+    pb = Problem(256, 128, 32)
+    rhs = I.rhs(pb, 54)
+    plan = [I.FaultEvent(t, vec, 20, start=t, count=1) for t in range(2, 40, every)]
+    s = ft.Solver(pb, kmax=3, max_steps=39)
+    assert _resident(ft, [s], lambda: s.solve(rhs, tol=1e-14, k=3, plan=plan[:-1]))
+    s.set_options(max_steps=38)
+    assert _resident(ft, [s], lambda: s.solve(rhs, tol=1e-14, k=3, plan=plan)) == resident
+    x, st = s.solve(rhs, tol=1e-14, k=3, plan=plan)
+    xo, so, _, _ = oracle_mod.Oracle(pb).solve(rhs, tol=1e-14, k=3, plan=plan, max_steps=38)
+    assert st["steps_executed"] == so["steps_executed"] == 38
+    assert st["detections"] == so["detections"] == 0
+    assert st["events_applied"] == so["events_applied"]
+    x, xo = x.cpu().numpy().ravel(), np.asarray(xo).ravel()
+    assert np.linalg.norm(x - xo) <= 1e-10 * np.linalg.norm(xo)
+    s.close()
