@@ -1478,7 +1478,63 @@ struct ResidentBatch {
     std::vector<int> rtx, nblk;   // per member
 };
 
-// Whether every member of the batch runs there (else the batch streams).
+// Launches of members with these blocks: first fit by falling counts, at most
+// `most` blocks in each.  bins: the indices into `blocks` of each launch.
+void first_fit(const std::vector<int>& blocks, int most, std::vector<std::vector<int>>& bins)
+{
+    std::vector<int> order(blocks.size()), room;
+    for (size_t q = 0; q < order.size(); ++q) order[q] = (int)q;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return blocks[a] > blocks[b]; });
+    bins.clear();
+    for (int q : order) {
+        size_t b = 0;
+        while (b < bins.size() && room[b] < blocks[q]) ++b;
+        if (b == bins.size()) {
+            bins.emplace_back();
+            room.push_back(most);
+        }
+        bins[b].push_back(q);
+        room[b] -= blocks[q];
+    }
+}
+
+// About the microseconds a step of the planned members with take(m) takes in
+// the resident kernel, and one of all members in streaming launches, with all of
+// them running.  Measured at k = 3 to 16 on 2 to 16 equal members of 25 sizes on
+// both meshes: launches of the resident kernel take 3% more per k beyond 3;
+// streaming launches 25 us, 5 a member and 19 (octahedral mesh: 23) a million
+// cells at the bytes of k = 3, in proportion to a step's bytes.  The two come
+// out on the wrong side of each other where they differ by a tenth at most.
+template <class Take>
+double batch_resident_us(const ResidentBatch& rb, int mesh, int k, int most, Take&& take)
+{
+    double us = 0.0;
+    for (const auto& d : rb.depths) {
+        std::vector<int> blocks;
+        for (int m : d.members)
+            if (take(m)) blocks.push_back(rb.nblk[m]);
+        std::vector<std::vector<int>> bins;
+        first_fit(blocks, most, bins);
+        us += (double)bins.size() * resident_step_us(mesh, d.H, 8, d.waves);
+    }
+    return us * (1.0 + 0.03 * (k - 3));
+}
+
+double batch_streaming_us(ftgcr_handle* const* hs, int n, int k)
+{
+    const double per = (hs[0]->geo.mesh == FTGCR_MESH_OCTAHEDRAL ? 23.0 : 19.0) * (10.0 + k + 3.0 / k) / 14.0;
+    double us = 25.0;
+    for (int m = 0; m < n; ++m) us += 5.0 + per * 1e-6 * (double)hs[m]->geo.n;
+    return us;
+}
+
+// Whether the batch runs there (else it streams): every member has to, and the
+// launches of one block per CU at most have to be quicker than streaming ones
+// over all members, which they are not where each holds a single member or two
+// of a million cells or less.  Microseconds a member and step, streaming and
+// resident, k = 3: 12 of 480 x 100 x 5 11, 16; 12 of 384 x 128 x 24 29, 36; 12 of
+// O_80 x 20 19, 26; 4 of O_60 x 17 17, 23; but 2 of them 23, 24, 2 of 384 x 128 x
+// 24 39, 38, 12 of 512 x 128 x 16 27, 24 and 12 of 128 x 64 x 16 7, 3.
 bool plan_resident_batch(ftgcr_handle* const* hs, int n, int k, ResidentBatch& rb)
 {
     // a tiling asked for in the options means the streaming kernels
@@ -1516,7 +1572,7 @@ bool plan_resident_batch(ftgcr_handle* const* hs, int n, int k, ResidentBatch& r
         }
         rb.depths.push_back({H, waves, d.second});
     }
-    return true;
+    return n == 1 || batch_resident_us(rb, mesh, k, most, [](int) { return true; }) < batch_streaming_us(hs, n, k);
 }
 
 // The steps of a batch planned by plan_resident_batch, from every member's
@@ -1583,8 +1639,6 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
         std::vector<Go> gos;
         bool streamed = false;
         for (const auto& d : rb.depths) {
-            std::vector<std::vector<int>> bins;   // members of one launch, first fit by falling block counts
-            std::vector<int> room;
             std::vector<Inst<double>> go_in;
             for (int m : d.members) {
                 if (host[2 * m] != RUNNING || (ahead && evp[m] >= evs[m].size())) continue;
@@ -1631,18 +1685,10 @@ ftgcr_status run_resident_batch(ftgcr_handle* const* hs, int n, int k, const Res
                 launched[m] = 1;
                 go_in.push_back(in);
             }
-            std::stable_sort(go_in.begin(), go_in.end(),
-                             [](const Inst<double>& a, const Inst<double>& b) { return a.nblk_res > b.nblk_res; });
-            for (int q = 0; q < (int)go_in.size(); ++q) {
-                size_t b = 0;
-                while (b < bins.size() && room[b] < go_in[q].nblk_res) ++b;
-                if (b == bins.size()) {
-                    bins.emplace_back();
-                    room.push_back(most);
-                }
-                bins[b].push_back(q);
-                room[b] -= go_in[q].nblk_res;
-            }
+            std::vector<int> blocks;
+            for (const auto& in : go_in) blocks.push_back(in.nblk_res);
+            std::vector<std::vector<int>> bins;   // members of one launch
+            first_fit(blocks, most, bins);
             for (const auto& bin : bins) {
                 Go go{&d, (int)pre.size(), (int)act.size(), (int)bin.size(), 0};
                 pre.push_back(0);

@@ -129,3 +129,26 @@ def test_events_in_close_succession(ft, oracle_mod, vec, every, resident):
     x, xo = x.cpu().numpy().ravel(), np.asarray(xo).ravel()
     assert np.linalg.norm(x - xo) <= 1e-10 * np.linalg.norm(xo)
     s.close()
+
+
+BATCHES = [([Problem(480, 100, 5)] * 6, False), ([Problem(480, 100, 5)] * 2, True), ([OctProblem(60, 17)] * 4, False),
+           ([OctProblem(16, 51)] * 4, True), ([Problem(128, 64, 16)] * 6, True),
+           ([Problem(384, 128, 24), Problem(64, 32, 8)], True)]
+
+
+@pytest.mark.parametrize("pbs,resident", BATCHES, ids=lambda v: str(len(v)) + "x" + str(v[0].shape) if isinstance(v, list) else str(v))
+def test_batches_that_pay(ft, oracle_mod, pbs, resident):
+    """Whichever runs, every member's first steps are the oracle's."""
+    print("[gpu-case] batches", len(pbs), pbs[0], flush=True)
+    solvers = [ft.Solver(pb, kmax=3, max_steps=8) for pb in pbs]
+    rhs = [I.rhs(pb, 55 + m) for m, pb in enumerate(pbs)]
+    assert _resident(ft, solvers, lambda: ft.solve_batch(solvers, rhs, tols=[1e-14] * len(pbs), k=3)) == resident
+    xs, sts = ft.solve_batch(solvers, rhs, tols=[1e-14] * len(pbs), k=3)
+    for m in {0, len(pbs) - 1}:
+        o = (oracle_mod.OctOracle if isinstance(pbs[m], OctProblem) else oracle_mod.Oracle)(pbs[m])
+        xo, _, _, _ = o.solve(rhs[m], tol=1e-14, k=3, max_steps=8)
+        assert sts[m]["steps_executed"] == 8
+        x, xo = xs[m].cpu().numpy().ravel(), np.asarray(xo).ravel()
+        assert np.linalg.norm(x - xo) <= 1e-10 * np.linalg.norm(xo)
+    for s in solvers:
+        s.close()
