@@ -20,6 +20,7 @@
 #include <cstddef>
 #include <cstring>
 #include <new>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -1502,8 +1503,9 @@ void first_fit(const std::vector<int>& blocks, int most, std::vector<std::vector
 // the resident kernel, and one of all members in streaming launches, with all of
 // them running.  Measured at k = 3 to 16 on 2 to 16 equal members of 25 sizes on
 // both meshes: launches of the resident kernel take 3% more per k beyond 3;
-// streaming launches 25 us, 5 a member and 19 (octahedral mesh: 23) a million
-// cells at the bytes of k = 3, in proportion to a step's bytes.  The two come
+// streaming launches 25 us, 5 a member (less on the smallest) and 18
+// (octahedral mesh: 21) a million cells, tiles counted whole, at the bytes of k =
+// 3, in proportion to a step's bytes.  The two come
 // out on the wrong side of each other where they differ by a tenth at most.
 template <class Take>
 double batch_resident_us(const ResidentBatch& rb, int mesh, int k, int most, Take&& take)
@@ -1522,9 +1524,13 @@ double batch_resident_us(const ResidentBatch& rb, int mesh, int k, int most, Tak
 
 double batch_streaming_us(ftgcr_handle* const* hs, int n, int k)
 {
-    const double per = (hs[0]->geo.mesh == FTGCR_MESH_OCTAHEDRAL ? 23.0 : 19.0) * (10.0 + k + 3.0 / k) / 14.0;
+    const bool oct = hs[0]->geo.mesh == FTGCR_MESH_OCTAHEDRAL;
+    const double per = (oct ? 21.0 : 18.0) * (10.0 + k + 3.0 / k) / 14.0;
     double us = 25.0;
-    for (int m = 0; m < n; ++m) us += 5.0 + per * 1e-6 * (double)hs[m]->geo.n;
+    for (int m = 0; m < n; ++m) {
+        const double cells = 1e-6 * (double)hs[m]->tx * hs[m]->ty * ST_THREADS * hs[m]->geo.nz;   // whole tiles
+        us += std::min(2.0 * per * cells, 5.0 + per * cells);
+    }
     return us;
 }
 
@@ -1575,8 +1581,56 @@ bool plan_resident_batch(ftgcr_handle* const* hs, int n, int k, ResidentBatch& r
     return n == 1 || batch_resident_us(rb, mesh, k, most, [](int) { return true; }) < batch_streaming_us(hs, n, k);
 }
 
+// Whether a planned batch takes its steps up to the last fault event in
+// streaming launches, all members together, before it goes on in the resident
+// kernel: there the members with events run ahead of the others from event to
+// event, a round of launches and a status read each (175 us), and a step with
+// an event in e is the member's alone; here a step with events costs a status
+// read (45 us).  Estimated over the steps a solve usually takes (50 a decade).
+// Microseconds a member and step over 100 steps, streaming and resident, 16 of
+// 64 x 32 x 8: flips in x in one member every second step 4.5, 7.2, every 16th
+// 2.8, 2.5; in e in all members every 8th 4.6, 7.5, every 50th 2.7, 2.1; 8 of
+// O_20 x 51: in x in one member every 4th 10.7, 12.9, every 50th 8.2, 7.5.
+bool stream_events_first(ftgcr_handle* const* hs, int n, int k, const ResidentBatch& rb,
+                         const std::vector<std::vector<DevEvent>>& evs, const double* tol)
+{
+    const int mesh = hs[0]->geo.mesh, most = std::min(hs[0]->cus, RES_BLOCKS);
+    std::set<long long> steps;   // with events
+    long long rounds = 0, events = 0, last = 0;
+    double alone = 0.0;   // members' own streaming steps
+    bool others = false;
+    std::vector<char> has(n, 0);
+    for (int m = 0; m < n; ++m) {
+        const long long usual = (long long)(50.0 * std::max(1.0, -std::log10(tol[m])));
+        long long mine = 0, at = 0, e_at = 0;
+        for (const DevEvent& ev : evs[m]) {
+            if (ev.step > usual) break;
+            if (ev.step != at) mine += 1;
+            at = ev.step;
+            if (ev.vec == FTGCR_V_E && ev.step != e_at) {   // that step, then a launch again
+                e_at = ev.step;
+                mine += 1;
+                alone += 33.0 + 18e-6 * (double)hs[m]->geo.n;
+            }
+            steps.insert(at);
+            events += 1;
+        }
+        has[m] = mine > 0;
+        others = others || mine == 0;
+        rounds = std::max(rounds, mine);
+        last = std::max(last, at);
+    }
+    if (events == 0) return false;
+    const double ahead = batch_resident_us(rb, mesh, k, most, [&](int m) { return has[m] != 0; });
+    const double all = batch_resident_us(rb, mesh, k, most, [](int) { return true; });
+    const double resident = 175.0 * rounds + 10.0 * events + alone + ahead * last;
+    const double streaming = 45.0 * steps.size() + 7.5 * (events - (long long)steps.size()) +
+                             (batch_streaming_us(hs, n, k) - (others ? all : 0.0)) * last;
+    return streaming < resident;
+}
+
 // The steps of a batch planned by plan_resident_batch, from every member's
-// start to its outcome.  Members with fault events ahead run first, each to
+// state to its outcome.  Members with fault events ahead run first, each to
 // the step before its next one; once none is left, all run to their end.  When
 // a launch does not run (its blocks do not start together, or the device does
 // not take it), the members still running are left to the streaming kernels:
@@ -1837,17 +1891,24 @@ ftgcr_status solve_batch_impl(ftgcr_handle* const* hs, int n, const double* cons
     };
     ResidentBatch rb;
     std::vector<long long> base(n, 0);   // a member's steps before `launched` counts
-    if (plan_resident_batch(hs, n, k, rb)) {
-        members.clear();
-        rc = run_resident_batch(hs, n, k, rb, ins, evs, tb_all, B.status, B.inst, B.blk0, members, base, evp, single,
-                                apply);
-        if (rc != FTGCR_OK) return rc;
-        if (!members.empty()) {
+    bool resident = plan_resident_batch(hs, n, k, rb);
+    bool events_first = resident && stream_events_first(hs, n, k, rb, evs, tol);
+    while (!members.empty()) {
+        if (events_first) {
+            events_first = false;
+            for (int m : members) events_first = events_first || evp[m] < evs[m].size();
+        }
+        if (resident && !events_first) {
+            resident = false;
+            members.clear();
+            launched = 0;
+            rc = run_resident_batch(hs, n, k, rb, ins, evs, tb_all, B.status, B.inst, B.blk0, members, base, evp, single,
+                                    apply);
+            if (rc != FTGCR_OK) return rc;
+            if (members.empty()) break;
             rc = upload_batch(h0, ins, members, H, B.inst, B.blk0, sh, tb);
             if (rc != FTGCR_OK) return rc;
         }
-    }
-    while (!members.empty()) {
         // fault events of the next step, member by member: x, r, p, L(p)
         // events now, e events between the step's decision and its stencil
         // pass

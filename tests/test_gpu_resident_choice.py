@@ -152,3 +152,31 @@ def test_batches_that_pay(ft, oracle_mod, pbs, resident):
         assert np.linalg.norm(x - xo) <= 1e-10 * np.linalg.norm(xo)
     for s in solvers:
         s.close()
+
+
+@pytest.mark.parametrize("vec", ["x", "r", "ap", "e"])
+@pytest.mark.parametrize("every", [1, 3, 30])
+@pytest.mark.parametrize("who", ["one", "all"])
+def test_batch_with_events(ft, oracle_mod, who, every, vec):
+    """Events in close succession in streaming launches of all members, the steps
+    after them and sparse events resident: every member as alone."""
+    print("[gpu-case] batch events", who, every, vec, flush=True)
+    pbs = [Problem(64, 32, 8), Problem(40, 20, 15), Problem(64, 32, 8, hill_lon=0.4)]
+    rhs = [I.rhs(pb, 58 + m) for m, pb in enumerate(pbs)]
+    plans = [[I.FaultEvent(t, vec, 51, start=t, count=5) for t in range(2 + m, 62, every)] if m == 1 or who == "all" else []
+             for m in range(len(pbs))]
+    plans[1].append(I.FaultEvent(70, "r", 62, start=3, count=1))
+    solvers = [ft.Solver(pb, kmax=3) for pb in pbs]
+    xs, sts = ft.solve_batch(solvers, rhs, tols=[1e-10] * len(pbs), k=3, plans=plans)
+    for m, pb in enumerate(pbs):
+        o = oracle_mod.Oracle(pb)
+        _, so, logo, _ = o.solve(rhs[m], tol=1e-10, k=3, plan=plans[m])
+        assert sts[m]["status"] == so["status"] == ft.CONVERGED
+        assert sts[m]["events_applied"] == so["events_applied"]
+        assert [(d["step"], d["nu"], d["action"]) for d in sts[m]["log"]] == [(d["step"], d["nu"], d["action"]) for d in logo]
+        assert abs(sts[m]["steps_executed"] - so["steps_executed"]) <= 1
+        xe, _, _, _ = o.solve(rhs[m], tol=1e-14, k=3, plan=plans[m], max_steps=sts[m]["steps_executed"])
+        x = xs[m].cpu().numpy().ravel()
+        assert np.linalg.norm(x - xe.ravel()) <= 1e-10 * np.linalg.norm(xe)
+    for s in solvers:
+        s.close()
