@@ -1255,7 +1255,7 @@ ftgcr_status gm_solve_impl(ftgcr_handle* h, const double* rhs, double* x, double
     const Table<double> tb{h->inst_dbg, h->blk0, h->blk0 + 2, h->blk0 + 4, 1, h->geo.mesh, h->precond};
     const int nblk_col = (h->geo.ncols + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
     const int nst = h->nblk_st, kc = h->kc;
-    const bool nt = nt_ap_hint(k, h->geo.n, (int)sizeof(double));
+    const bool nt = gm_nt_hint(k, h->geo.n);
     GmState* hs = h->gm_host;
     auto read_head = [&]() -> ftgcr_status {
         HIP_TRY(h, hipGetLastError());

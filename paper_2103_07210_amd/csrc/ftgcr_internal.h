@@ -353,7 +353,7 @@ struct GmLaunch {
     static void restart(const GmInst* gi, hipStream_t s);
     static void precond(const Table<double>& tb, const GmInst* gi, int nblk_col, int H, hipStream_t s);
     // dots = 0: store A z_j only (the dots follow a fault event on it)
-    // nt: the basis does not fit the cache (nt_ap_hint)
+    // nt: the basis does not fit the cache (gm_nt_hint)
     static void stencil(const GmInst* gi, int nblk_st, int kc, int dots, int mesh, bool nt, hipStream_t s);
     static void dots(const GmInst* gi, int nblk_st, int kc, hipStream_t s);
     static void finish_h(const GmInst* gi, hipStream_t s);
@@ -382,6 +382,18 @@ int thomas_depth(int nz);
 inline bool nt_ap_hint(int k, long long n_total, int elem)
 {
     return (double)(k + 1) * (double)n_total * elem > 192.0 * 1024 * 1024;
+}
+
+// Whether FT-GMRES should load its Krylov vectors so: when besides they are so
+// long that the few a step writes and reads again (z_j, w, v_{j+1}) do not stay
+// cached behind the others.  Below 32 MiB a vector the others are still found
+// there in part: microseconds a step without and with the hint, k = 16, 300 x 150
+// x 40 (14 MB a vector) 98, 108; O_90 x 51 (15) 97, 112; 430 x 215 x 40 (30) 184,
+// 193; 480 x 240 x 40 (37) 218, 206; 480 x 240 x 60 (55) 325, 298; k = 8, 430 x
+// 215 x 40 138, 146; 480 x 240 x 40 157, 156; 480 x 240 x 60 239, 223.
+inline bool gm_nt_hint(int k, long long n)
+{
+    return nt_ap_hint(k, n, 8) && (double)n * 8.0 > 32.0 * 1024 * 1024;
 }
 
 }  // namespace ftgcr

@@ -2231,7 +2231,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_gm_restart(const GmInst* gi)
 // v_{i+1} are issued before v_i's values are used (two buffers alternating
 // with the parity of i), so the terms cost one memory round trip together
 // rather than one each.
-// NT: the Arnoldi vectors are loaded with the non-temporal hint (nt_ap_hint:
+// NT: the Arnoldi vectors are loaded with the non-temporal hint (gm_nt_hint:
 // the cycle's vectors do not fit the Infinity Cache, which is then left to
 // z_j, w and v_{j+1}, read again within the step: FT-GMRES(16) on 512 x 256 x
 // 64 308.6 -> 271.5 ms, the stencil pass 150 -> 130 us, orthogonalisation 124
