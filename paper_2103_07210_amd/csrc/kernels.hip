@@ -1424,14 +1424,17 @@ __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init
         acc_d = fma(ad, ad, acc_d);
     }
     if (last) {
-        // p^k and the iterate: sums over the basis in ascending order
-        double xa[KC];
+        // p^k and the iterate: sums over the basis in ascending order, the
+        // iterate's update by itself, so that it is rounded once a cycle and
+        // not once a term
+        double xa[KC], xd[KC];
         T ub[2][KC];
         const gptr<T> u0 = as_global(s_u[0]);
 #pragma unroll
         for (int kk = 0; kk < KC; ++kk) {
             const int kq = (ps.k0 + kk > nz - 1) ? nz - 1 : ps.k0 + kk;
             xa[kk] = __builtin_nontemporal_load(&xb[c0 + plane * kq]);
+            xd[kk] = 0.0;
             ub[0][kk] = __builtin_nontemporal_load(&u0[c0 + plane * kq]);
         }
 #pragma unroll
@@ -1449,7 +1452,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk) {
                     p[kk] = fma(pj, (double)ub[j & 1][kk], p[kk]);
-                    xa[kk] = fma(xj, (double)ub[j & 1][kk], xa[kk]);
+                    xd[kk] = fma(xj, (double)ub[j & 1][kk], xd[kk]);
                 }
             }
         }
@@ -1458,7 +1461,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_dir_update(Table<T> tb, int init
             if (ps.col_ok && ps.k0 + kk < nz) {
                 const long long c = c0 + plane * (ps.k0 + kk);
                 __builtin_nontemporal_store((T)p[kk], &pout[c]);
-                __builtin_nontemporal_store(xa[kk], &xo[c]);
+                __builtin_nontemporal_store(xa[kk] + xd[kk], &xo[c]);
             }
         }
     }
@@ -1515,10 +1518,10 @@ __global__ __launch_bounds__(ST_THREADS) void k_finalize_x(Table<T> tb)
     for (int kk = 0; kk < KC; ++kk) {
         if (ps.k0 + kk < in.g.nz) {
             const long long c = (long long)ps.i + (long long)in.g.nx * ps.j + (long long)in.g.ncols * (ps.k0 + kk);
-            double xa = xb[c];
+            double xd = 0.0;
             if (hi >= lo)
-                for (int j = 0; j <= hi; ++j) xa = fma(s_c[j], (double)as_global(s_u[j])[c], xa);
-            xo[c] = xa;
+                for (int j = 0; j <= hi; ++j) xd = fma(s_c[j], (double)as_global(s_u[j])[c], xd);
+            xo[c] = xb[c] + xd;
         }
     }
 }
@@ -1607,10 +1610,10 @@ __global__ void k_event_copy(Table<T> tb)
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n; c += stride) {
         if (vec == FTGCR_V_X) {
-            double xa = in.X[st->ev_src][c];
+            double xd = 0.0;
             if (st->ev_hi > st->ev_lo)
-                for (int j = 0; j < st->ev_hi; ++j) xa = fma(s_c[j], (double)in.U[st->uslot[j]][c], xa);
-            in.X[st->ev_dst][c] = xa;
+                for (int j = 0; j < st->ev_hi; ++j) xd = fma(s_c[j], (double)in.U[st->uslot[j]][c], xd);
+            in.X[st->ev_dst][c] = in.X[st->ev_src][c] + xd;
         } else if (vec == FTGCR_V_R) {
             in.R[st->ev_dst][c] = in.R[st->ev_src][c];
         } else if (st->ev_copy == 2) {

@@ -797,7 +797,9 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
             }
         }
         __syncthreads();
-        if (lastp) {   // p^k and the iterate from the basis
+        // p^k and the iterate from the basis: its update is summed by itself,
+        // so the iterate is rounded once a cycle and not once a term
+        if (lastp) {
             const double* const xb = uniform(in.X[s_st.x_base]);
             double* const xo = uniform(in.X[s_st.x_dst]);
             const T* const ue = uniform((const T*)s_u[nu + 1]);
@@ -807,7 +809,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
 #pragma unroll
             for (int c0 = 0; c0 < H; c0 += CL) {
                 fence_rows();
-                double p[CL], x[CL];
+                double p[CL], d[CL], x[CL];
                 unsigned ax[CL];
                 T v[2][CL], ev[CL];
                 const T* u0 = uniform((const T*)s_u[0]);
@@ -817,11 +819,13 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
                     settle(ax[c]);
                     ax[c] *= XS;
                     v[0][c] = *elem(u0, at[c0 + c]);
-                    x[c] = *elem(xb, ax[c]);
                     ev[c] = *elem(ue, at[c0 + c]);
                 }
 #pragma unroll
-                for (int c = 0; c < CL; ++c) p[c] = (double)ev[c];
+                for (int c = 0; c < CL; ++c) {
+                    p[c] = (double)ev[c];
+                    d[c] = 0.0;
+                }
                 for (int q = 0; q <= nu; q += 2) {
 #pragma unroll
                     for (int b = 0; b < 2; ++b) {
@@ -835,11 +839,13 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
 #pragma unroll
                             for (int c = 0; c < CL; ++c) {
                                 p[c] = fma(pj, (double)v[b][c], p[c]);
-                                x[c] = fma(xj, (double)v[b][c], x[c]);
+                                d[c] = fma(xj, (double)v[b][c], d[c]);
                             }
                         }
                     }
                 }
+#pragma unroll
+                for (int c = 0; c < CL; ++c) x[c] = *elem(xb, ax[c]);
                 if (stores) {
 #pragma unroll
                     for (int c = 0; c < CL; ++c) {
@@ -849,7 +855,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
                         const int q = c0 + c;
                         if (q < pad_rows(H) && q < H - nmine) continue;
                         *elem_mut(pout, at[q]) = (T)p[c];
-                        *elem_mut(xo, ax[c]) = x[c];
+                        *elem_mut(xo, ax[c]) = x[c] + d[c];
                     }
                 }
             }
