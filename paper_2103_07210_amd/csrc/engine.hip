@@ -340,9 +340,9 @@ double streaming_step_us(const ftgcr_handle* h)
 // it its exchange words.  A grid it does not take, a device without cooperative
 // launches, or a form of the kernel that takes longer than the streaming
 // kernels on this grid leaves the handle to those.  Such forms are the ones
-// that spill: us a step, streaming and resident, binary32 O_119 x 64 74, 90,
-// O_87 x 64 59, 77, O_87 x 33 44, 47 (but O_119 x 33 54, 52), 512 x 128 x 64 74,
-// 78, O_12 x 96 31, 33; FP64 O_87 x 17 40, 47 (but O_119 x 32 67, 59).
+// that spill: us a step, streaming and resident, binary32 O_87 x 33 44, 47 (but
+// O_119 x 33 54, 52), O_12 x 96 31, 33; FP64 O_87 x 17 40, 47 (but O_119 x 32 67,
+// 59).
 ftgcr_status setup_resident(ftgcr_handle* h)
 {
     if (h->precond != FTGCR_PRECOND_COLUMN) return FTGCR_OK;

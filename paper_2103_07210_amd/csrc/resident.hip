@@ -901,10 +901,11 @@ __global__ __launch_bounds__(64 * MAXW) void k_resident(const Inst<T>* insts, co
 
 // Registers bound the depth: a half column of H levels holds five vectors of
 // H values per lane (r, L(p), the pivots, e, L(e)), 512 registers at one
-// wavefront per SIMD (four to a block), 256 at two.
+// wavefront per SIMD (four to a block), 256 at two; the deepest of each spill
+// some (resident_step_us).
 bool resident_shape(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int waves, int* rtx, int* nblk)
 {
-    const int hmax = waves <= 4 ? (elem_bytes == 4 ? 48 : 32) : (elem_bytes == 4 ? 32 : 16);
+    const int hmax = waves <= 4 ? (elem_bytes == 4 ? 48 : 32) : (elem_bytes == 4 ? 28 : 16);
     const int most = cus < RES_BLOCKS ? cus : RES_BLOCKS;
     if (H > hmax) return false;
     const bool oct = mesh == FTGCR_MESH_OCTAHEDRAL;
@@ -928,17 +929,20 @@ int resident_waves(int mesh, int nx, int ny, int H, int elem_bytes, int cus, int
 // 48) and wavefronts per block (1, 2, 4, 8).  It hardly depends on the grid: a
 // block runs its columns' rows in sequence whatever the number of blocks.  What
 // steps up between the columns of a row is registers: at eight wavefronts FP64
-// halves of 16 and binary32 ones of 24 rows and more spill (up to 300 vector
-// registers of 256), at four binary32 ones of 48.
+// halves of 16 rows spill 113 to 202 vector registers beyond their 256, binary32
+// ones of 24 and 28 rows 117 to 224; at four FP64 ones of 32 rows up to 16,
+// binary32 ones of 40 rows 26 and of 48 rows 65.  (Binary32 halves of 32 rows at
+// eight spilled 288: 78 us lat-lon and 84 octahedral, where the largest grid of
+// that form streams in 75.)
 double resident_step_us(int mesh, int H, int elem_bytes, int waves)
 {
     static const unsigned char us[2][2][4][8] = {   // mesh; FP64, binary32; wavefronts; depth
         {{{11, 12, 15, 18, 20, 21}, {13, 14, 18, 21, 23, 25}, {14, 16, 22, 27, 30, 31}, {18, 22, 37}},
          {{11, 12, 14, 17, 19, 20, 23, 28}, {13, 14, 17, 20, 22, 23, 28, 33}, {14, 15, 19, 24, 26, 28, 34, 42},
-          {16, 19, 25, 41, 60, 78}}},
+          {16, 19, 25, 41, 60}}},
         {{{11, 12, 15, 19, 22, 24}, {13, 15, 19, 24, 26, 29}, {14, 17, 25, 29, 36, 41}, {19, 25, 50}},
          {{12, 12, 15, 19, 21, 22, 27, 33}, {13, 14, 18, 22, 25, 26, 33, 40}, {14, 16, 19, 24, 28, 30, 38, 46},
-          {16, 19, 25, 50, 68, 84}}}};
+          {16, 19, 25, 50, 68}}}};
     const int depths[] = {4, 8, 16, 24, 28, 32, 40, 48};
     int d = 0, w = 0;
     while (d < 7 && depths[d] < H) ++d;
@@ -956,7 +960,7 @@ const void* resident_kernel(int mesh, int H, int waves)
         if (waves <= 4)                                                                                   \
             return mesh == FTGCR_MESH_OCTAHEDRAL ? (const void*)k_resident<T, HV, FTGCR_MESH_OCTAHEDRAL, 4> \
                                                  : (const void*)k_resident<T, HV, FTGCR_MESH_LATLON, 4>;  \
-        if constexpr (sizeof(T) == 4 || HV <= 16)                                                         \
+        if constexpr (HV <= (sizeof(T) == 4 ? 28 : 16))                                                   \
             return mesh == FTGCR_MESH_OCTAHEDRAL ? (const void*)k_resident<T, HV, FTGCR_MESH_OCTAHEDRAL, 8> \
                                                  : (const void*)k_resident<T, HV, FTGCR_MESH_LATLON, 8>;  \
         return nullptr;
