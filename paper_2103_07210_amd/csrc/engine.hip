@@ -746,6 +746,9 @@ struct Runner {
     // no allocation of any kind: no graph capture or instantiation, no
     // timing events (kernel timing and graph replay are skipped)
     bool noalloc = false;
+    // a resident launch's blocks did not start together: this solve streams
+    // (in all its refinement rounds, so that it waits for them once)
+    bool late = false;
 
     long long cur_step = 0;
 
@@ -897,7 +900,6 @@ struct Runner {
         double rr_prev = -1.0;
         long long s_prev = 0;
         bool resident_norms = false;   // the state's norms are the resident kernel's
-        bool late = false;             // its blocks did not start together: this solve streams
         std::vector<const DevEvent*> on_r;   // events on r before the launch
         auto back_to_streaming = [&]() {     // the launch did not run
             if (resident_norms) streaming_norms<T>(tb, on_r, h->nblk_col, h->H, s);
