@@ -22,11 +22,11 @@ import sys
 from collections import defaultdict
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-KERNELS_SRC = os.path.join(ROOT, "paper_2103_07210_amd", "csrc", "kernels.hip")
+CSRC = os.path.join(ROOT, "paper_2103_07210_amd", "csrc")
 
 
-def source_sha256() -> str:
-    return hashlib.sha256(open(KERNELS_SRC, "rb").read()).hexdigest()
+def source_sha256(name="kernels.hip") -> str:
+    return hashlib.sha256(open(os.path.join(CSRC, name), "rb").read()).hexdigest()
 
 
 def _dispatches(outdir):
@@ -51,6 +51,8 @@ def stats(outdir, cmd):
     print("# rocprofv3 kernel trace summary\n")
     print(f"command: `{cmd}`\n")
     print(f"kernels.hip sha256: {source_sha256()}\n")
+    if any("k_resident" in name for name, _ in rows):
+        print(f"resident.hip sha256: {source_sha256('resident.hip')}\n")
     print("| kernel | dispatches | total ms | avg us | dispatches > 20 us | avg us (> 20 us) |")
     print("|---|---|---|---|---|---|")
     for name, durs in rows[:24]:
